@@ -18,15 +18,15 @@
 //     snake order, so every CU gets a similar share of tiles.  Per 64-key
 //     tile, K is staged row-major and V row-major with its rows interleaved
 //     within 16-key blocks (read back through transposing LDS reads free of
-//     bank conflicts); with values by direct-to-LDS loads into five K
-//     and four V stages, two tiles per barrier; statistics only through
-//     registers, one tile per barrier.  Each wave computes
+//     bank conflicts); with values by direct-to-LDS loads into four K
+//     and five V stages, two tiles per barrier; statistics only into four K
+//     stages, one tile per barrier.  Each wave computes
 //     S^T = K Q^T with v_mfma_f32_32x32x16_bf16 so that every lane holds 16
 //     keys of one pair column and the online softmax runs in-lane; the
 //     probabilities feed O^T = V^T P^T straight from the accumulator
-//     registers.  The loop is software-pipelined by 32-key sub-tiles: the S^T
-//     products of the next sub-tile are issued while the current one is
-//     exponentiated.  A block whose keys form a single split writes its final
+//     registers.  The loop is software-pipelined by 32-key sub-tiles: while a
+//     sub-tile is exponentiated, the S^T products of the next one and (with
+//     values) the O^T products of the previous one are issued.  A block whose keys form a single split writes its final
 //     outputs; otherwise each split writes (m, l, O) partials in the log2
 //     domain.
 //  3. combine_kernel merges the partials of split blocks in a fixed order
@@ -61,9 +61,9 @@ struct TileGeom {
   static_assert(KT * kPitch * 2 % 1024 == 0 && KT * vPitch * 2 % 1024 == 0, "whole 1 KB transfers");
 };
 
-// With values: five K and four V tile stages filled by direct-to-LDS loads
-// (160.8 KB at d = 128).  Statistics only: three register-staged K tiles, the
-// key-domain bits and the image table.
+// With values: four K and five V tile stages filled by direct-to-LDS loads
+// (158 KB at d = 128).  Statistics only: four K stages, the key-domain bits and
+// the image table.
 template <bool Stats>
 struct StatsLds {
   uint64_t okmask[4];  // key-domain filter per K stage, bit = key
@@ -74,8 +74,8 @@ struct StatsLds<false> {};
 
 template <int D, bool PV>
 struct AttnSmem : StatsLds<!PV> {
-  alignas(16) u16 k[PV ? 5 : 4][KT][TileGeom<D>::kPitch];
-  alignas(16) u16 v[PV ? 4 : 1][PV ? KT : 1][TileGeom<D>::vPitch];
+  alignas(16) u16 k[4][KT][TileGeom<D>::kPitch];
+  alignas(16) u16 v[PV ? 5 : 1][PV ? KT : 1][TileGeom<D>::vPitch];
 };
 
 // One 1 KB direct-to-LDS transfer: lane l's 16 bytes at byte voff of the
@@ -83,7 +83,7 @@ struct AttnSmem : StatsLds<!PV> {
 // compiler's wait insertion does not make every later LDS read wait for it;
 // completion is awaited explicitly (vm_wait) before the barrier that
 // publishes a tile.
-__device__ __forceinline__ void lds_dma16(__amdgpu_buffer_rsrc_t r, uint32_t lds_addr, uint32_t voff) {
+__device__ __forceinline__ void lds_dma16(u32x4 r, uint32_t lds_addr, uint32_t voff) {
   asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                :
                : "s"(lds_addr), "v"(voff), "s"(r)
@@ -99,6 +99,11 @@ __device__ __forceinline__ void vm_wait() {
 
 __device__ __forceinline__ int row_position(const int32_t *row_pos, int q_pos0, int r) {
   return row_pos ? row_pos[r] : q_pos0 + r;
+}
+
+__device__ __forceinline__ int4 scalar4(const int4 &v) {
+  return make_int4(__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y),
+                   __builtin_amdgcn_readfirstlane(v.z), __builtin_amdgcn_readfirstlane(v.w));
 }
 
 // Closed-form plan of rows at q_pos0 + r: block pb's {maxpos, minpos, n_s,
@@ -330,7 +335,7 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
 
   const int G = p.group;
   const int n_pairs = p.n_rows * G;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int col = lane & 31, half = lane >> 5;
   if (p.zero_i32)
     for (int i = blockIdx.x * kThreads + tid; i < p.zero_n; i += gridDim.x * kThreads) p.zero_i32[i] = 0;
@@ -340,28 +345,51 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
   const KvPageReader pr = page_reader(p.pages, p.n_ctx);
   using Geo = TileGeom<D>;
   const int v_lane = v_operand_lane_offset_il<Geo::vPitch>(lane);  // PV operand reads (interleaved V rows)
-  // Direct-to-LDS staging (with values): a tile's K transfers are numbered
-  // 0..kXfer-1 and its V transfers kXfer..kXfer+vXfer-1; wave w issues
-  // transfers w, w + 8, ...  Lane l of transfer x fills LDS byte 16 l of it,
-  // i.e. one 16-byte chunk of a padded row; lanes that land in the padding
-  // point past the buffer's end, so they fetch nothing and write zeros.
-  // xoff[s] is lane l's byte offset inside the tile for transfer wave + 8 s
-  // (head offset added per item; the padding offset stays out of range).
-  constexpr int kXferAll = Geo::kXfer + Geo::vXfer;
+  // Direct-to-LDS staging: a tile is a row of 1 KB transfers; lane l of
+  // transfer x fills LDS byte 16 l of it, i.e. one 16-byte chunk of a padded
+  // row; lanes that land in the padding point past the buffer's end, so they
+  // fetch nothing and write zeros.  k_off(x) / v_off(x): lane l's byte offset
+  // inside the tile's cache rows.
   constexpr uint32_t kPadOff = 0x80000000u;  // beyond any tile resource (< 2 GiB): reads as 0
-  constexpr int kXferUsed = PV ? kXferAll : Geo::kXfer;  // statistics only: K tiles alone
-  constexpr int kSlots = (kXferUsed + W - 1) / W;
-  uint32_t xoff0[kSlots];
+  auto k_off = [&](int x) __attribute__((always_inline)) {
+    const int b = x * 1024 + 16 * lane, row = b / (2 * Geo::kPitch), ch = (b % (2 * Geo::kPitch)) / 16;
+    return ch < D / 8 ? (uint32_t)row * (uint32_t)(2 * p.k_stride) + 16u * ch : kPadOff;
+  };
+  auto v_off = [&](int x) __attribute__((always_inline)) {
+    const int b = x * 1024 + 16 * lane, lrow = b / (2 * Geo::vPitch), ch = (b % (2 * Geo::vPitch)) / 16;
+    // V rows are stored interleaved: LDS row lrow holds this key of the tile
+    const int row = (lrow & ~15) | v_interleaved_key(lrow & 15);
+    return ch < D / 8 ? (uint32_t)row * (uint32_t)(2 * p.v_stride) + 16u * ch : kPadOff;
+  };
+  // Wave w issues transfers w, w + W, ... of a K tile.  With values, tiles
+  // come in groups of two K and two V tiles: each wave takes transfers w,
+  // w + W, ... below the last whole multiple of W of every tile, and one of
+  // the group's left-over transfers (waves past the last one repeat it: the
+  // same bytes to the same place), so that every wave issues the same number
+  // with no branch.
+  constexpr int kFull = Geo::kXfer / W, vFull = Geo::vXfer / W;
+  constexpr int kLeft = Geo::kXfer % W, vLeft = Geo::vXfer % W;
+  constexpr int kSlots = PV ? kFull : (Geo::kXfer + W - 1) / W;
+  static_assert(!PV || 2 * (kLeft + vLeft) <= W, "one left-over transfer per wave");
+  uint32_t ko[kSlots], vo[PV ? vFull : 1], xo = 0;
 #pragma unroll
   for (int sl = 0; sl < kSlots; ++sl) {
-    const int x = wave + W * sl;
-    const bool isk = x < Geo::kXfer;
-    const int pitch_b = 2 * (isk ? Geo::kPitch : Geo::vPitch);
-    const int b = (isk ? x : x - Geo::kXfer) * 1024 + 16 * lane;
-    const int lrow = b / pitch_b, ch = (b % pitch_b) / 16;
-    // V rows are stored interleaved: LDS row lrow holds this key of the tile
-    const int row = isk ? lrow : (lrow & ~15) | v_interleaved_key(lrow & 15);
-    xoff0[sl] = ch < D / 8 ? (uint32_t)(((int64_t)row * (isk ? p.k_stride : p.v_stride) + 8 * ch) * 2) : kPadOff;
+    ko[sl] = k_off(wave + W * sl);
+    asm volatile("" : "+v"(ko[sl]));  // one register each (else the division that formed it is kept as a pair)
+  }
+  const int left = min(wave, 2 * (kLeft + vLeft) - 1);  // left-over transfer: Ka.., Kb.., Va.., Vb..
+  const int left_x = left < 2 * kLeft ? kFull * W + left % (kLeft > 0 ? kLeft : 1)
+                                      : vFull * W + (left - 2 * kLeft) % (vLeft > 0 ? vLeft : 1);
+  const bool left_k = left < 2 * kLeft;
+  const bool left_b = left_k ? left >= kLeft : left >= 2 * kLeft + vLeft;  // of the group's second tile
+  if constexpr (PV) {
+#pragma unroll
+    for (int sl = 0; sl < vFull; ++sl) {
+      vo[sl] = v_off(wave + W * sl);
+      asm volatile("" : "+v"(vo[sl]));
+    }
+    xo = left_k ? k_off(left_x) : v_off(left_x);
+    asm volatile("" : "+v"(xo));
   }
   const u16 *Qg = static_cast<const u16 *>(p.q);
   void *o_out = p.o_out;
@@ -400,14 +428,15 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
       slot_off = (int64_t)layer * p.plan.max_items;
     }
     const int uns = p.plan.uniform_ns;
+    // (the plan's entries are the same in every lane: kept in scalar registers)
     const int4 item = uniform ? make_int4((idx / uns) % p.n_kv_heads, idx / (uns * p.n_kv_heads), idx % uns, idx)
-                              : p.plan.items[idx];  // {kv head, block, split, slot}
+                              : scalar4(p.plan.items[idx]);  // {kv head, block, split, slot}
     const int kvh = item.x, pb = item.y;
     if (kvh < 0 || kvh >= p.n_kv_heads || pb < 0 || pb >= p.plan.n_pb || item.w < 0 ||
         item.w >= p.plan.max_items)
       continue;
     const int4 info = uniform ? uniform_block_info(pb, kPairs, G, p.n_rows, p.q_pos0, p.n_ctx, uns)
-                              : p.plan.pb_info[pb];  // {maxpos, minpos, n_s, chunk}
+                              : scalar4(p.plan.pb_info[pb]);  // {maxpos, minpos, n_s, chunk}
     const int kbeg = item.z * info.w;
     const int kend = min(kbeg + info.w, info.x + 1);
     const int minpos = info.y;
@@ -440,30 +469,65 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
         }
       }
     };
-    // This wave's transfers of the K tile at t0 (row0; rows at or past kend
-    // read as 0 through the resource bound) into K stage st, or (with values)
-    // of the V tile into V stage st.  A tile that does not exist still
-    // gets its transfers (zero-length resource), so every iteration issues
-    // the same count per wave.
+    // The buffer resource of the K (or V) tile at t0, whose first token sits
+    // in cache row `row`: this KV head's bytes of its rows; rows at or past
+    // kend, and tiles that do not exist, read as 0 through its bound.  Kept
+    // in scalar registers (its inputs are uniform).  A cache holds fewer than
+    // 2^32 rows (a row is at least 128 bytes), so the row's byte offset is a
+    // 32 x 32-bit product.
     const uint32_t head_b = (uint32_t)(kvh * D * 2);
-    auto dma_tile = [&](bool isk, int st, int t0, int64_t row0) __attribute__((always_inline)) {
-      {
-        const int rows = min(max(kend - t0, 0), KT);
-        // the resource must sit in scalar registers: its inputs are uniform,
-        // which readfirstlane makes explicit
-        const uint64_t ga = (uint64_t)(uintptr_t)(isk ? Kg + row0 * p.k_stride : Vg + row0 * p.v_stride);
-        const uint64_t gu = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(ga >> 32)) << 32) |
-                            (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)ga);
-        const int nbytes = __builtin_amdgcn_readfirstlane((int)(rows * (isk ? p.k_stride : p.v_stride) * 2));
-        const auto rs = buffer_rsrc(reinterpret_cast<const void *>((uintptr_t)gu), nbytes);
-        const uint32_t base = isk ? (uint32_t)(uintptr_t)&sm.k[st][0][0] : (uint32_t)(uintptr_t)&sm.v[PV ? st : 0][0][0];
+    const uint32_t k_row_b = 2u * (uint32_t)p.k_stride, v_row_b = 2u * (uint32_t)p.v_stride;
+    const uint64_t k_base = (uint64_t)(uintptr_t)Kg + head_b, v_base = (uint64_t)(uintptr_t)Vg + head_b;
+    auto tile_rsrc = [&](uint64_t base, uint32_t row_b, int t0, uint32_t row) __attribute__((always_inline)) {
+      const uint64_t ga = base + (uint64_t)row * row_b;
+      const int rows = min(max(kend - t0, 0), KT);
+      u32x4 r;
+      r[0] = __builtin_amdgcn_readfirstlane((uint32_t)ga);
+      r[1] = __builtin_amdgcn_readfirstlane((uint32_t)(ga >> 32));
+      r[2] = __builtin_amdgcn_readfirstlane((uint32_t)max((int)(rows * row_b) - (int)head_b, 0));
+      r[3] = kRawBufferWord3;
+      return r;
+    };
+    auto k_stage = [&](int st) __attribute__((always_inline)) { return (uint32_t)(uintptr_t)&sm.k[st][0][0]; };
+    auto v_stage = [&](int st) __attribute__((always_inline)) { return (uint32_t)(uintptr_t)&sm.v[PV ? st : 0][0][0]; };
+    // This wave's transfers of the K tile at t0 into K stage st.
+    auto dma_k = [&](int st, int t0, uint32_t row) __attribute__((always_inline)) {
+      const u32x4 rs = tile_rsrc(k_base, k_row_b, t0, row);
 #pragma unroll
-        for (int sl = 0; sl < kSlots; ++sl) {
-          const int x = wave + W * sl;
-          if (isk ? x < Geo::kXfer : (x >= Geo::kXfer && x < kXferAll))
-            lds_dma16(rs, __builtin_amdgcn_readfirstlane(base + (isk ? x : x - Geo::kXfer) * 1024),
-                      xoff0[sl] == kPadOff ? kPadOff : xoff0[sl] + head_b);
+      for (int sl = 0; sl < kSlots; ++sl)
+        if (PV || wave + W * sl < Geo::kXfer)
+          lds_dma16(rs, __builtin_amdgcn_readfirstlane(k_stage(st) + (wave + W * sl) * 1024), ko[sl]);
+      if constexpr (PV) {
+        if (wave < kLeft)
+          lds_dma16(rs, __builtin_amdgcn_readfirstlane(k_stage(st) + (kFull * W + wave) * 1024), xo);
+      }
+    };
+    // A group of transfers: K tiles into stages k0, k1 and V tiles into v0, v1.
+    struct Group {
+      u32x4 k0, k1, v0, v1;
+    };
+    constexpr int kGroupXfers = 2 * (kFull + vFull) + 1;  // per wave
+    // Transfer n of this wave's share of a group.
+    auto dma_group = [&](const Group &gr, int sk0, int sk1, int sv0, int sv1, int n) __attribute__((always_inline)) {
+      if (n < 2 * vFull) {
+        lds_dma16(n & 1 ? gr.v1 : gr.v0,
+                  __builtin_amdgcn_readfirstlane(v_stage(n & 1 ? sv1 : sv0) + (wave + W * (n / 2)) * 1024),
+                  vo[PV ? n / 2 : 0]);
+      } else if (n < 2 * vFull + 2 * kFull) {
+        const int i = n - 2 * vFull;
+        lds_dma16(i & 1 ? gr.k1 : gr.k0,
+                  __builtin_amdgcn_readfirstlane(k_stage(i & 1 ? sk1 : sk0) + (wave + W * (i / 2)) * 1024),
+                  ko[i / 2]);
+      } else {
+        u32x4 r;
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+          const uint32_t a = left_k ? gr.k0[e] : gr.v0[e], b = left_k ? gr.k1[e] : gr.v1[e];
+          r[e] = left_b ? b : a;
         }
+        r[3] = kRawBufferWord3;
+        const uint32_t a = left_k ? k_stage(sk0) : v_stage(sv0), b = left_k ? k_stage(sk1) : v_stage(sv1);
+        lds_dma16(r, __builtin_amdgcn_readfirstlane((left_b ? b : a) + left_x * 1024), xo);
       }
     };
 
@@ -511,29 +575,26 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
     };
 
     // Software-pipelined main loop over 64-key tiles of two 32-key
-    // sub-tiles, one barrier per tile.  Each sub-step issues the S^T products
-    // of the next sub-tile while it exponentiates the current one
-    // (independent work in one instruction stream, so the matrix core and
-    // the VALU overlap), then O^T += V^T P^T of the current sub-tile while it
-    // takes the next one's maximum.  Iteration t reads K(t), K(t+1) and V(t).
-    // With values the tiles arrive by direct-to-LDS loads into a four-stage
-    // ring, K three tiles ahead and V two (each wave waits for the transfers
-    // it issued one iteration earlier before the barrier); statistics only
-    // stage K through registers one tile ahead (three K buffers).
+    // sub-tiles: each sub-step issues the S^T products of the next sub-tile
+    // while it exponentiates the current one (independent work in one
+    // instruction stream, so the matrix core and the VALU overlap).
     // Block-table entries of 64 consecutive tiles are read at once, one per
     // lane, and each tile takes its entry with a lane read; only every 64th
     // tile waits for the table.
     int page_vec = 0, page_base = -64;
-    auto tile_row = [&](int t0) __attribute__((always_inline)) {
+    // Makes the entries of the tile at t0 and of the two after it available
+    // (a tile past kend may take any row: its resource is empty).
+    auto pages_for = [&](int t0) __attribute__((always_inline)) {
       const int ti = t0 / KT;
-      if (ti - page_base >= 64) {
+      if (ti + 2 - page_base >= 64) {
         page_base = ti;
-        page_vec = read_page(pr, (ti + (tid & 63)) * KT);
+        page_vec = read_page(pr, (ti + lane) * KT);
         vm_wait<0>();  // here, not before every lane read (the tile transfers are invisible to the compiler)
       }
-      return page_row(pr, __builtin_amdgcn_readlane(page_vec, ti - page_base), t0);
     };
-    auto row_of = [&](int t0) __attribute__((always_inline)) { return t0 < kend ? tile_row(t0) : (int64_t)0; };
+    auto tile_row = [&](int t0) __attribute__((always_inline)) {
+      return (uint32_t)page_row(pr, __builtin_amdgcn_readlane(page_vec, t0 / KT - page_base), t0);
+    };
 
     // With values, the probabilities of an item are taken against one
     // reference maximum per pair column, fixed for the item: the first
@@ -569,21 +630,26 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
     }
     if constexpr (PV) {
       // K(0..2), V(0..1); tiles past kend arrive as zeros
-      const int64_t r0 = tile_row(kbeg), r1 = row_of(kbeg + KT), r2 = row_of(kbeg + 2 * KT);
-      dma_tile(true, 0, kbeg, r0);
-      dma_tile(false, 0, kbeg, r0);
-      dma_tile(true, 1, kbeg + KT, r1);
-      dma_tile(false, 1, kbeg + KT, r1);
-      dma_tile(true, 2, kbeg + 2 * KT, r2);
+      pages_for(kbeg);
+      const uint32_t r0 = tile_row(kbeg), r1 = tile_row(kbeg + KT), r2 = tile_row(kbeg + 2 * KT);
+      Group g0;
+      g0.k0 = tile_rsrc(k_base, k_row_b, kbeg, r0);
+      g0.k1 = tile_rsrc(k_base, k_row_b, kbeg + KT, r1);
+      g0.v0 = tile_rsrc(v_base, v_row_b, kbeg, r0);
+      g0.v1 = tile_rsrc(v_base, v_row_b, kbeg + KT, r1);
+#pragma unroll
+      for (int n = 0; n < kGroupXfers; ++n) dma_group(g0, 0, 1, 0, 1, n);
+      dma_k(2, kbeg + 2 * KT, r2);
       vm_wait<0>();
     } else {
       // K(0..2); tiles past kend arrive as zeros
-      const int64_t r0 = tile_row(kbeg), r1 = row_of(kbeg + KT), r2 = row_of(kbeg + 2 * KT);
-      dma_tile(true, 0, kbeg, r0);
+      pages_for(kbeg);
+      const uint32_t r0 = tile_row(kbeg), r1 = tile_row(kbeg + KT), r2 = tile_row(kbeg + 2 * KT);
+      dma_k(0, kbeg, r0);
       okmask_tile(0, kbeg);
-      dma_tile(true, 1, kbeg + KT, r1);
+      dma_k(1, kbeg + KT, r1);
       okmask_tile(1, kbeg + KT);
-      dma_tile(true, 2, kbeg + 2 * KT, r2);
+      dma_k(2, kbeg + 2 * KT, r2);
       okmask_tile(2, kbeg + 2 * KT);
       vm_wait<0>();
     }
@@ -595,40 +661,29 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
       m_seen = m;
       over = false;
     }
-    // One sub-step.  cur holds S^T of the current sub-tile (sub-tile csub of
-    // the tile at ct0, K stage cbuf; its V rows are vsub*32.. of V stage
-    // vst); the S^T products of the next sub-tile (K stage kbn, rows
-    // ksub*32..; after the last sub-tile: discarded) are issued into nxt.
-    // The key filter of cur comes first, so everything after it is one basic
-    // block: the compiler then places the exponentials of cur among the
-    // matrix products of nxt instead of sinking them past a later branch.
-    // exact_tag std::false_type (a first attempt with a fixed reference)
-    // only checks that the sub-tile's probabilities stay below 2^kHeadroom
-    // in sum, which any sub-tile exceeding the reference by more than
-    // kHeadroom violates.  std::true_type: with values every sub-tile's
-    // maximum is tracked against the reference (the attempts after a
-    // restart); statistics keep the online maximum.
-    auto sub_step = [&](auto exact_tag, f32x16 &cur, f32x16 &nxt, int kbn, int ksub, int vst, int vsub,
-                        bool cur_masked, int cbuf, int ct0, int csub) __attribute__((always_inline)) {
+    // One sub-step of the statistics.  cur holds S^T of the current sub-tile
+    // (sub-tile csub of the tile at ct0, K stage cbuf); the S^T products of
+    // the next sub-tile (K stage kbn, rows ksub*32..; after the last
+    // sub-tile: discarded) are issued into nxt.  The key filter of cur comes
+    // first, so everything after it is one basic block: the compiler then
+    // places the exponentials of cur among the matrix products of nxt instead
+    // of sinking them past a later branch.  exact_tag std::false_type (a
+    // first attempt with a fixed reference) only checks that the sub-tile's
+    // probabilities stay below 2^kHeadroom in sum, which any sub-tile
+    // exceeding the reference by more than kHeadroom violates;
+    // std::true_type keeps the online maximum.
+    auto sub_step = [&](auto exact_tag, f32x16 &cur, f32x16 &nxt, int kbn, int ksub, bool cur_masked, int cbuf,
+                        int ct0, int csub) __attribute__((always_inline)) {
       constexpr bool kExact = decltype(exact_tag)::value;
       if (cur_masked) mask_sub(cur, cbuf, ct0, csub);
       nxt = scores(kbn, ksub);
       float alpha = 1.f;
-      if constexpr (PV) {
-        if constexpr (kExact) {
-          const float mx = sub_max(cur);
-          m_seen = fmaxf(m_seen, mx);
-          over = over || mx > m + kHeadroom;
-        }
-      } else if constexpr (kExact) {
+      if constexpr (kExact) {
         const float mx = sub_max(cur);
         const bool grow = mx > m + kRescaleSlack;
         alpha = grow ? fast_exp2(m - mx) : 1.f;
         m = grow ? mx : m;
       }
-      // probabilities of the current sub-tile; fp32 row sum (the
-      // log-sum-exp output needs it to 1e-4; summing the bf16-rounded
-      // probabilities is off by up to 2^-9 when few terms dominate)
       const float neg_m = -m;
 #pragma unroll
       for (int v = 0; v < 16; ++v) cur[v] = fast_exp2(fmaf(cur[v], c, neg_m));
@@ -636,71 +691,181 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
 #pragma unroll
       for (int v = 0; v < 16; ++v) psum += cur[v];
       if constexpr (!kExact) over = over || !(psum <= kHeadroomSum);  // inf included
-      l = PV || !kExact ? l + psum : l * alpha + psum;
+      l = !kExact ? l + psum : l * alpha + psum;
       // l is needed only after the loop; this empty statement makes it (and
       // so this sub-tile's exponentials) due here, so the compiler does not
       // sink them past the next sub-step's key filter.
       asm volatile("" ::"v"(l));
-      if constexpr (PV) {
-        bf16x8 pk[2];
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) pk[ks][e] = static_cast<__bf16>(cur[8 * ks + e]);
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-          bf16x8 va[DT];
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt)
-            va[dt] = v_operand_il<Geo::vPitch>(&sm.v[vst][vsub * 32 + ks * 16][dt * 32] + v_lane);
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt)
-            o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[dt], pk[ks], o[dt], 0, 0, 0);
-        }
-      }
     };
     const int gen = ++attempt_id;  // the workgroup's attempts in order (uniform, never repeats)
     bool restart = false;
     if constexpr (PV) {
-      // Two tiles (t, t+1) per barrier.  K stages rotate mod 5 and V stages
-      // mod 4: the iteration reads K(t..t+2) and V(t..t+1) while K(t+3),
-      // K(t+4), V(t+2) and V(t+3) arrive; they are awaited before the
-      // barrier, one iteration after they were issued.  A tile t+1 past kend
-      // arrives as zeros and is masked whole.  The last iteration issues no
-      // transfers: only a next iteration would read them.
-      // The first attempt checks the probability sums, a restart tracks the
-      // maxima (below).
-      auto tiles = [&](auto exact_tag) __attribute__((always_inline)) {
-      int t0 = kbeg, ks = 0, vs = 0;  // stages of tile t
-      for (;;) {
-        const int k1 = ks + 1 == 5 ? 0 : ks + 1, k2 = k1 + 1 == 5 ? 0 : k1 + 1;
-        const int k3 = k2 + 1 == 5 ? 0 : k2 + 1, k4 = k3 + 1 == 5 ? 0 : k3 + 1;
-        const int v1 = (vs + 1) & 3, v2 = (vs + 2) & 3, v3 = (vs + 3) & 3;
-        const bool more2 = t0 + 2 * KT < kend;  // the next iteration exists
-        if (more2) {
-          const int64_t r2 = row_of(t0 + 2 * KT), r3 = row_of(t0 + 3 * KT), r4 = row_of(t0 + 4 * KT);
-          dma_tile(false, v2, t0 + 2 * KT, r2);
-          dma_tile(false, v3, t0 + 3 * KT, r3);
-          dma_tile(true, k3, t0 + 3 * KT, r3);
-          dma_tile(true, k4, t0 + 4 * KT, r4);
+      // Sub-step i (32 keys) holds three independent pieces of work, one
+      // matrix product and its share of the other two per slot:
+      //   S^T(i+1) from K operands, P(i) = 2^(c S^T(i) - m) on the VALU, and
+      //   O^T += V^T(i-1) P^T(i-1).
+      // Operands pass through one register ring: a sub-step's S^T products
+      // take the K operands read during the previous sub-step and leave the
+      // V operands of its own O^T products behind, which in turn leave the
+      // K operands of sub-tile i + 2, so every LDS read has eight products'
+      // time to arrive.  The slots are fixed by scheduling barriers: left to
+      // itself the compiler reads each operand one product ahead and
+      // gathers the VALU work behind the products, and the two waves of a
+      // SIMD then take turns between the matrix core and the VALU.  Shader
+      // cycles of the whole kernel at 66,816 keys and 6,553 rows (28/4 heads
+      // of 128): 6.28 M before, 5.25 M in this order (matrix cores busy 50%
+      // and 60%); the clock drops from 1.85 to 1.67 GHz meanwhile (the chip's
+      // power limit), so the call went from 3.12 to 2.92 ms.
+      //
+      // Two tiles (t, t+1) per barrier.  K stages rotate mod 4 and V stages
+      // mod 5: the iteration reads K(t+1), K(t+2) and V(t-1), V(t), V(t+1)
+      // while K(t+3), K(t+4), V(t+2) and V(t+3) arrive, issued one transfer
+      // every few slots (in one go at the iteration's start they cost the
+      // products about 3%), planned during the previous iteration's last
+      // sub-step and awaited before the barrier.  A tile past kend arrives as
+      // zeros (its resource is empty) and is masked whole.
+      constexpr int kPv = 2 * DT;       // products of a sub-step's O^T update
+      static_assert(kPv == KS, "one operand ring serves both product chains");
+      constexpr int kSlots2 = KS + kPv, kEps = 16 / kSlots2;
+      bf16x8 ring[KS], pk[2];
+#pragma unroll
+      for (int j = 0; j < KS; ++j) ring[j] = as_bf16x8(ld16(&sm.k[0][32 + col][8 * half] + j * 16));
+      pk[0] = pk[1] = as_bf16x8(u32x4{0, 0, 0, 0});
+      // cur: S^T(i); nxt: receives S^T(i+1) from the ring; K operands read:
+      // stage kst, rows ksub * 32..; V operands: stage vst, rows vsub * 32..;
+      // sub-tile i is sub-tile csub of the tile at ct0.  hook(j): the
+      // transfers' part of slot j.
+      auto pv_step = [&](bool masked, f32x16 &cur, f32x16 &nxt, int kst, int ksub, int vst, int vsub, int ct0,
+                         int csub, auto hook) __attribute__((always_inline)) {
+        if (masked) mask_sub(cur, 0, ct0, csub);
+        if (!fixed_ref) {
+          const float mx = sub_max(cur);
+          m_seen = fmaxf(m_seen, mx);
+          over = over || mx > m + kHeadroom;
         }
+        const float neg_m = -m;
+        const u16 *krow = &sm.k[kst][ksub * 32 + col][8 * half];
+        const u16 *vrow = &sm.v[vst][vsub * 32][0] + v_lane;
+        // probabilities of sub-tile i; fp32 row sum (the log-sum-exp output
+        // needs it to 1e-4; summing the bf16-rounded probabilities is off by
+        // up to 2^-9 when few terms dominate).  The empty statements keep
+        // each value's computation in its slot.
+        u32x4 pn[2];
+        float pe[16];
+        auto pack = [&](int e) __attribute__((always_inline)) {
+          bf16x2 w;
+          w[0] = static_cast<__bf16>(pe[e]);
+          w[1] = static_cast<__bf16>(pe[e + 1]);
+          const uint32_t u = __builtin_bit_cast(uint32_t, w);
+          asm volatile("" ::"v"(u));
+          pn[e / 8][(e % 8) / 2] = u;
+        };
+        float psum = 0.f;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < kSlots2; ++j) {
+          if (j < KS) {
+            nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[j], qreg[j], j == 0 ? f32x16{} : nxt, 0, 0, 0);
+            if (j & 1) {
+              ring[j] = v_operand_il<Geo::vPitch>(vrow + (j / DT) * 16 * Geo::vPitch + (j % DT) * 32);
+              ring[j - 1] = v_operand_il<Geo::vPitch>(vrow + ((j - 1) / DT) * 16 * Geo::vPitch + ((j - 1) % DT) * 32);
+            }
+          } else {
+            const int jj = j - KS, k2 = jj / DT, dt = jj % DT;
+            o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[jj], pk[k2], o[dt], 0, 0, 0);
+            if (jj & 1) {
+              ring[jj] = as_bf16x8(ld16(krow + jj * 16));
+              ring[jj - 1] = as_bf16x8(ld16(krow + (jj - 1) * 16));
+            }
+          }
+#pragma unroll
+          for (int e = j * kEps; e < (j + 1) * kEps; ++e) {
+            pe[e] = fast_exp2(fmaf(cur[e], c, neg_m));
+            asm volatile("" ::"v"(pe[e]));
+            if (e >= 1) {
+              psum += pe[e - 1];
+              asm volatile("" ::"v"(psum));
+            }
+            if (e >= 3 && (e & 1)) pack(e - 3);
+          }
+          hook(j);
+          if (j == kSlots2 - 1) {
+            psum += pe[15];
+            asm volatile("" ::"v"(psum));
+            pack(14);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        over = over || (fixed_ref && !(psum <= kHeadroomSum));  // inf included
+        l += psum;
+        asm volatile("" ::"v"(l));
+        pk[0] = as_bf16x8(pn[0]);
+        pk[1] = as_bf16x8(pn[1]);
+      };
+      int vlast = 0;
+      int t0 = kbeg, ks = 0, vs = 0;  // stages of tile t
+      Group gr;
+      // The next iteration's transfers: K(t+3), K(t+4), V(t+2), V(t+3), in
+      // four parts (rows, then resources).
+      uint32_t r2, r3, r4;
+      auto plan_part = [&](int part, int t) __attribute__((always_inline)) {
+        if (part == 0) {
+          pages_for(t + 2 * KT);
+          r2 = tile_row(t + 2 * KT);
+          r3 = tile_row(t + 3 * KT);
+          r4 = tile_row(t + 4 * KT);
+        } else if (part == 1) {
+          gr.v0 = tile_rsrc(v_base, v_row_b, t + 2 * KT, r2);
+        } else if (part == 2) {
+          gr.v1 = tile_rsrc(v_base, v_row_b, t + 3 * KT, r3);
+        } else if (part == 3) {
+          gr.k0 = tile_rsrc(k_base, k_row_b, t + 3 * KT, r3);
+        } else if (part == 4) {
+          gr.k1 = tile_rsrc(k_base, k_row_b, t + 4 * KT, r4);
+        }
+      };
+      constexpr int kPlanParts = 5, kPlanStep = kSlots2 / kPlanParts;
+      static_assert(kPlanStep >= 1 && kPlanStep * (kPlanParts - 1) < kSlots2, "every part has a slot");
+#pragma unroll
+      for (int i = 0; i < kPlanParts; ++i) plan_part(i, t0);
+      for (;;) {
+        const int k1 = (ks + 1) & 3, k2 = (ks + 2) & 3, k3 = (ks + 3) & 3;
+        const int v1 = vs + 1 == 5 ? 0 : vs + 1, v2 = v1 + 1 == 5 ? 0 : v1 + 1, v3 = v2 + 1 == 5 ? 0 : v2 + 1;
+        const bool more2 = t0 + 2 * KT < kend;  // the next iteration exists
         const bool m0 = tile_masked(t0), m1 = tile_masked(t0 + KT);
-        sub_step(exact_tag, sa, sb, ks, 1, vs, 0, m0, ks, t0, 0);       // S(t,1)   | P(t,0) V
-        sub_step(exact_tag, sb, sa, k1, 0, vs, 1, m0, ks, t0, 1);       // S(t+1,0) | P(t,1) V
-        sub_step(exact_tag, sa, sb, k1, 1, v1, 0, m1, k1, t0 + KT, 0);  // S(t+1,1) | P(t+1,0) V
-        sub_step(exact_tag, sb, sa, k2, 0, v1, 1, m1, k1, t0 + KT, 1);  // S(t+2,0) | P(t+1,1) V
+        // kSpread slots between two transfers
+        constexpr int kSpread = 2 * kSlots2 / (kGroupXfers + 1);
+        static_assert(kSpread >= 1 && kSpread * kGroupXfers <= 2 * kSlots2, "every transfer has a slot");
+        auto issue = [&](int g) __attribute__((always_inline)) {
+          if (g % kSpread == kSpread - 1 && g / kSpread < kGroupXfers) dma_group(gr, k3, ks, v2, v3, g / kSpread);
+        };
+        pv_step(m0, sa, sb, k1, 0, vlast, 1, t0, 0,     // P(t,0)   | S(t,1)   | PV(t-1,1)
+                [&](int j) __attribute__((always_inline)) { issue(j); });
+        pv_step(m0, sb, sa, k1, 1, vs, 0, t0, 1,        // P(t,1)   | S(t+1,0) | PV(t,0)
+                [&](int j) __attribute__((always_inline)) { issue(kSlots2 + j); });
+        pv_step(m1, sa, sb, k2, 0, vs, 1, t0 + KT, 0,   // P(t+1,0) | S(t+1,1) | PV(t,1)
+                [&](int) __attribute__((always_inline)) {});
+        pv_step(m1, sb, sa, k2, 1, v1, 0, t0 + KT, 1,   // P(t+1,1) | S(t+2,0) | PV(t+1,0)
+                [&](int j) __attribute__((always_inline)) {
+                  if (j % kPlanStep == 0 && j / kPlanStep < kPlanParts) plan_part(j / kPlanStep, t0 + 2 * KT);
+                });
+        vlast = v1;
         if (__ballot(over) != 0 && lane == 0) s_restart = gen;
         vm_wait<0>();
         __syncthreads();
-        restart = s_restart == gen;
+        restart = __builtin_amdgcn_readfirstlane(s_restart) == gen;
         if (!more2 || restart) break;
         t0 += 2 * KT;
         ks = k2;
         vs = v2;
       }
-      };
-      if (fixed_ref) tiles(std::false_type{});
-      else tiles(std::true_type{});
+      if (!restart) {
+        const u16 *vrow = &sm.v[vlast][32][0] + v_lane;
+#pragma unroll
+        for (int jj = 0; jj < kPv; ++jj)
+          o[jj % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              v_operand_il<Geo::vPitch>(vrow + (jj / DT) * 16 * Geo::vPitch + (jj % DT) * 32), pk[jj / DT], o[jj % DT], 0, 0, 0);
+      }
     } else {
       // One tile per barrier, K stages mod 4: iteration t reads K(t) and
       // K(t+1) while K(t+2) is complete and K(t+3) arrives.  Before the
@@ -716,19 +881,20 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
         const bool need3 = t0 + 2 * KT < kend;  // iteration t+2 exists
         const int st1 = (st + 1) & 3, st3 = (st + 3) & 3;
         if (need3) {
-          dma_tile(true, st3, t0 + 3 * KT, row_of(t0 + 3 * KT));
+          pages_for(t0 + 3 * KT);
+          dma_k(st3, t0 + 3 * KT, tile_row(t0 + 3 * KT));
           okmask_tile(st3, t0 + 3 * KT);
         }
         const bool m0 = tile_masked(t0);
-        sub_step(exact_tag, sa, sb, st, 1, 0, 0, m0, st, t0, 0);   // S(t,1)   | P(t,0)
-        sub_step(exact_tag, sb, sa, st1, 0, 0, 0, m0, st, t0, 1);  // S(t+1,0) | P(t,1)
+        sub_step(exact_tag, sa, sb, st, 1, m0, st, t0, 0);   // S(t,1)   | P(t,0)
+        sub_step(exact_tag, sb, sa, st1, 0, m0, st, t0, 1);  // S(t+1,0) | P(t,1)
         if constexpr (!kExact) {
           if (__ballot(over) != 0 && lane == 0) s_restart = gen;
         }
         if (need3) vm_wait<kSlots - 1>();
         else vm_wait<0>();
         __syncthreads();
-        if constexpr (!kExact) restart = s_restart == gen;
+        if constexpr (!kExact) restart = __builtin_amdgcn_readfirstlane(s_restart) == gen;
         if (!more || restart) break;
         t0 += KT;
         st = st1;
@@ -771,6 +937,8 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
       // the rows are assembled in LDS (pair-major, the K stages: no tile is
       // read any more) and written out 16 bytes per lane, each pair's row
       // contiguous.
+      int otid = tid;  // opaque, so that no address below is formed before the tile loop and held through it
+      asm volatile("" : "+v"(otid));
       static_assert(kPairs * Geo::kPitch <= (int)(sizeof(sm.k) / 2), "output rows fit the K stages");
       u16 *orow = &sm.k[0][0][0];
       const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
@@ -781,7 +949,7 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
           uint2 w;
           w.x = (uint32_t)f32_to_bf16(o[dt][4 * g4] * inv) | ((uint32_t)f32_to_bf16(o[dt][4 * g4 + 1] * inv) << 16);
           w.y = (uint32_t)f32_to_bf16(o[dt][4 * g4 + 2] * inv) | ((uint32_t)f32_to_bf16(o[dt][4 * g4 + 3] * inv) << 16);
-          *reinterpret_cast<uint2 *>(orow + (wave * 32 + col) * Geo::kPitch + dt * 32 + 8 * g4 + 4 * half) = w;
+          *reinterpret_cast<uint2 *>(orow + ((otid >> 6) * 32 + (otid & 31)) * Geo::kPitch + dt * 32 + 8 * g4 + 4 * ((otid >> 5) & 1)) = w;
         }
       __syncthreads();
       constexpr int kChunks = D / 8;  // 16-byte pieces of a row
@@ -789,7 +957,7 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
       u16 *const obase = single ? static_cast<u16 *>(o_out) : p.part_o + (item.w + slot_off) * kPairs * D;
 #pragma unroll 2
       for (int i = 0; i < kPairs * kChunks / kThreads; ++i) {
-        const int c = tid + kThreads * i;
+        const int c = otid + kThreads * i;
         const int pl = c / kChunks, ch = c % kChunks;
         const int pr = pair0 + pl;
         if (pr < n_pairs) {

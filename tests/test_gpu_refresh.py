@@ -226,3 +226,44 @@ def test_merge_refresh_equals_separate_calls(case):
                                          L["q_star"][sel], rows)
     r = np.asarray(list(rows))
     assert_attention(to_f64(out)[r], o_ref[r], w.dtype, what="O")
+
+
+def _attend64(q, k, v, pos):
+    """Causal attention of rows at `pos` in float64 on the device: output and log-sum-exp."""
+    n, hq, d = q.shape
+    hkv = k.shape[1]
+    g = hq // hkv
+    out = torch.empty(n, hq, d, dtype=torch.float64, device=DEV)
+    lse = torch.empty(n, hq, dtype=torch.float64, device=DEV)
+    key = torch.arange(k.shape[0], device=DEV)
+    for h in range(hkv):
+        kh, vh = k[:, h].double(), v[:, h].double()
+        for r0 in range(0, n, 512):
+            r1 = min(n, r0 + 512)
+            z = (q[r0:r1, h * g:(h + 1) * g].double().reshape(-1, d) @ kh.t() / d ** 0.5).view(r1 - r0, g, -1)
+            z.masked_fill_((key[None, :] > pos[r0:r1, None])[:, None, :], -torch.inf)
+            lse[r0:r1, h * g:(h + 1) * g] = torch.logsumexp(z, dim=2)
+            out[r0:r1, h * g:(h + 1) * g] = (torch.softmax(z, dim=2).view(-1, len(key)) @ vh).view(r1 - r0, g, d)
+    return out, lse
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_ctx,n_rows,hkv,g", [(1, 1, 1, 1), (63, 9, 2, 2), (64, 64, 1, 4), (65, 3, 2, 7), (128, 20, 1, 4),
+                                                (129, 40, 2, 7), (256, 33, 4, 1), (321, 100, 2, 4), (450, 450, 1, 8),
+                                                (513, 70, 4, 7), (4900, 1500, 8, 4), (12837, 4600, 8, 4)])
+def test_refresh_tile_pipeline(d, n_ctx, n_rows, hkv, g):
+    """Key ranges of one tile up to about two hundred in one item, whole and ragged, odd and even tile counts: every
+    stage of the tile ring and of the sub-step pipeline is read and refilled.  Every row against float64; bf16
+    probabilities and outputs (2^-9 each) bound the relative L2 error of a row."""
+    gen = torch.Generator(device=DEV).manual_seed(n_ctx * 131 + d)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device=DEV).to(torch.bfloat16)
+    k, v, q = rnd(n_ctx, hkv, d), rnd(n_ctx, hkv, d), rnd(n_rows, hkv * g, d)
+    pos = torch.sort(torch.randperm(n_ctx, generator=gen, device=DEV)[:n_rows]).values
+    pos[-1] = n_ctx - 1
+    out = torch.empty_like(q)
+    lse = torch.empty(n_rows, hkv * g, dtype=torch.float32, device=DEV)
+    api.conduit_refresh_attn(api.kv_desc(k, v, hkv * g), q, pos.to(torch.int32), out, lse_out=lse)
+    ref, ref_lse = _attend64(q, k, v, pos)
+    err = (out.double() - ref).norm(dim=2) / ref.norm(dim=2)
+    assert float(err.max()) < 1e-2
+    assert float((lse.double() - ref_lse).abs().max()) < 1e-4

@@ -20,21 +20,15 @@ constexpr int64_t kMaxSpanBytes = int64_t(1) << 31;
 
 // Epoch of a statistics launch's merge marks (never 0): a mark written
 // under another epoch counts as unset, so the workspace needs no clearing
-// between calls.
+// before its first call.  Counter values are scattered over 32 bits (an odd
+// multiplier permutes them), so that small integers that another call left in
+// the workspace are not taken for marks.
 uint32_t next_merge_epoch() {
   static std::atomic<uint32_t> epoch{0};
   uint32_t e;
-  do e = ++epoch;
+  do e = ++epoch * 0x9e3779b1u;
   while (e == 0);
   return e;
-}
-
-// Whether the column-sum workgroups rebuild the split statistics rows
-// themselves (small spans and caches) rather than the statistics kernel
-// merging each block once.
-bool colsum_fuses_lse(int32_t lse_ns, int64_t n_pair, int32_t n_vis) {
-  return lse_ns > 1 && lse_ns <= kLseRegSplits && n_pair <= kColsumMaxLsePairs &&
-         (n_vis + kColsumKeysPerBlock - 1) / kColsumKeysPerBlock <= kColsumFuseMaxBlocks;
 }
 
 namespace {
@@ -392,8 +386,6 @@ conduit_status conduit_score(const conduit_kv *kv, const void *q, int32_t n_q, i
   float *row_b = reinterpret_cast<float *>(at(ws, L.row_b));
   const bool vis_only = norm == CONDUIT_NORM_VISUAL_ONLY;
 
-  int32_t lse_ns = 0;
-  bool fuse_lse = false;
   DirectOut f32_stats{};  // fp32: the statistics' outputs (key splits merged by the column sums)
   hipError_t e;
   // bf16: the column-sum workgroups count their arrivals per key block and
@@ -432,14 +424,10 @@ conduit_status conduit_score(const conduit_kv *kv, const void *q, int32_t n_q, i
       ap.plan = plan_at(ws, L.plan);
       ap.part_m = reinterpret_cast<float *>(at(ws, L.plan.part_m));
       ap.part_l = reinterpret_cast<float *>(at(ws, L.plan.part_l));
-      // split rows: merged by the column-sum workgroups, or else by the
-      // statistics kernel's last split of each block (no merge launch)
-      lse_ns = attn_span_splits(ap, attn_pairs_per_block(false), 1);
-      fuse_lse = colsum_fuses_lse(lse_ns, (int64_t)n_q * ap.group, img->n_vis);
-      if (!fuse_lse) {
-        ap.merge_flag = reinterpret_cast<uint32_t *>(at(ws, L.merge_flag));
-        ap.epoch = next_merge_epoch();
-      }
+      // split rows: merged by the statistics kernel's last split of each
+      // block (no merge launch)
+      ap.merge_flag = reinterpret_cast<uint32_t *>(at(ws, L.merge_flag));
+      ap.epoch = next_merge_epoch();
       ap.skip_merge = 1;
       ap.zero_i32 = done;
       ap.zero_n = n_done;
@@ -492,12 +480,9 @@ conduit_status conduit_score(const conduit_kv *kv, const void *q, int32_t n_q, i
     cs.lse_ns = f32_stats.n_split;
     cs.lse_out = row_lse_out;
   }
-  if (fuse_lse) {
-    cs.lse_part_m = reinterpret_cast<float *>(at(ws, L.plan.part_m));
-    cs.lse_part_l = reinterpret_cast<float *>(at(ws, L.plan.part_l));
-    cs.lse_ns = lse_ns;
-    cs.lse_ppb = attn_pairs_per_block(false);
-    cs.lse_out = row_lse_out;
+  if (bf16 && !row_lse_in) {
+    cs.clear_u32 = reinterpret_cast<uint32_t *>(at(ws, L.merge_flag));
+    cs.clear_n = L.plan.max_items;
   }
   cs.done = done;
   cs.fin = fp;
@@ -594,7 +579,7 @@ conduit_status conduit_score_layers(const conduit_kv *kvs, int32_t n_layers, con
   ap.plan = plan_at(ws, L.plan);
   ap.part_m = reinterpret_cast<float *>(at(ws, L.plan.part_m));
   ap.part_l = reinterpret_cast<float *>(at(ws, L.plan.part_l));
-  ap.skip_merge = 1;  // merged by the column sums or by the statistics kernel (split count per launch, below)
+  ap.skip_merge = 1;  // merged by the statistics kernel
   ap.zero_i32 = done;
   ap.zero_n = n_done;
 
@@ -627,8 +612,9 @@ conduit_status conduit_score_layers(const conduit_kv *kvs, int32_t n_layers, con
   fp.a_acc = a_acc;
 
   // Per batch of up to 16 layers: one statistics launch (which also clears
-  // the finalize counters and merges its split rows) and one column-sum launch whose last workgroup per
-  // key block finalizes the batch's layers in order onto s_acc and A.
+  // the finalize counters and merges its split rows) and one column-sum
+  // launch whose last workgroup per key block finalizes the batch's layers in
+  // order onto s_acc and A.
   for (int32_t l0 = 0; l0 < n_layers; l0 += kMaxLayerBatch) {
     LayerTable lt{};
     lt.n = std::min<int32_t>(kMaxLayerBatch, n_layers - l0);
@@ -639,18 +625,11 @@ conduit_status conduit_score_layers(const conduit_kv *kvs, int32_t n_layers, con
       lt.rowb[i] = row_b + i * rows;
       lt.vnorm[i] = vnorm_in ? vnorm_in[l0 + i] : nullptr;
     }
-    // The statistics' split count depends on the launch's layer count; the
-    // column sums rebuild the split rows themselves when they can, otherwise
-    // the statistics kernel merges them (each launch marks afresh).
-    const int32_t lse_ns = attn_span_splits(ap, attn_pairs_per_block(false), lt.n);
-    const bool fuse_lse = colsum_fuses_lse(lse_ns, (int64_t)n_q * ap.group, img->n_vis);
-    ap.merge_flag = fuse_lse ? nullptr : reinterpret_cast<uint32_t *>(at(ws, L.merge_flag));
-    if (!fuse_lse) ap.epoch = next_merge_epoch();
-    cs.lse_part_m = fuse_lse ? ap.part_m : nullptr;
-    cs.lse_part_l = fuse_lse ? ap.part_l : nullptr;
-    cs.lse_ns = fuse_lse ? lse_ns : 0;
-    cs.lse_ppb = fuse_lse ? attn_pairs_per_block(false) : 0;
-    cs.lse_layer_stride = fuse_lse ? (int64_t)L.plan.max_items * attn_pairs_per_block(false) : 0;
+    // the statistics kernel merges its split rows (each launch marks afresh)
+    ap.merge_flag = reinterpret_cast<uint32_t *>(at(ws, L.merge_flag));
+    ap.epoch = next_merge_epoch();
+    cs.clear_u32 = ap.merge_flag;
+    cs.clear_n = (int32_t)(L.plan.max_items * lt.n);
     hipError_t e = launch_attn(ap, D, false, stream, &lt);
     if (e != hipSuccess) return hip_fail(e, "row statistics");
     fp.accumulate = (l0 > 0 || accumulate) ? 1 : 0;

@@ -19,16 +19,16 @@
 //     tile, K is staged row-major and V row-major with its rows interleaved
 //     within 16-key blocks (read back through transposing LDS reads free of
 //     bank conflicts); with values by direct-to-LDS loads into four K
-//     and five V stages, two tiles per barrier; statistics only into four K
-//     stages, one tile per barrier.  Each wave computes
+//     and five V stages (statistics only: four K stages), two tiles per
+//     barrier.  Each wave computes
 //     S^T = K Q^T with v_mfma_f32_32x32x16_bf16 so that every lane holds 16
 //     keys of one pair column and the online softmax runs in-lane; the
 //     probabilities feed O^T = V^T P^T straight from the accumulator
 //     registers.  The loop is software-pipelined by 32-key sub-tiles: while a
 //     sub-tile is exponentiated, the S^T products of the next one and (with
-//     values) the O^T products of the previous one are issued.  A block whose keys form a single split writes its final
-//     outputs; otherwise each split writes (m, l, O) partials in the log2
-//     domain.
+//     values) the O^T products of the previous one are issued.  A block
+//     whose keys form a single split writes its final outputs; otherwise each
+//     split writes (m, l, O) partials in the log2 domain.
 //  3. combine_kernel merges the partials of split blocks in a fixed order
 //     (deterministic, no atomics).
 #include <algorithm>
@@ -48,7 +48,7 @@ constexpr float kMInit = -1e30f;  // initial running maximum (log2 units)
 // and l is rescaled rarely.  Exact: l and the final normaliser share it.
 constexpr float kRescaleSlack = 8.f;
 // Statistics: split partials a merging workgroup loads at once per pair.
-constexpr int kMergeLoads = 16;
+constexpr int kMergeLoads = 24;
 
 // LDS tiles.  K rows are D + 8 elements apart (16 bytes of padding: the 16
 // lanes of an S^T operand read cover 16 rows in distinct banks); V rows are
@@ -66,7 +66,8 @@ struct TileGeom {
 // the image table.
 template <bool Stats>
 struct StatsLds {
-  uint64_t okmask[4];  // key-domain filter per K stage, bit = key
+  float2 ml[128];      // {m, l} of the odd-sub-tile waves' pair columns
+  uint64_t okmask[8];  // key-domain filter of tile t of the item at t mod 8, bit = key
   ImageLds img;        // visual-only statistics: the image table
 };
 template <>
@@ -79,15 +80,16 @@ struct AttnSmem : StatsLds<!PV> {
 };
 
 // One 1 KB direct-to-LDS transfer: lane l's 16 bytes at byte voff of the
-// buffer land at LDS byte lds_addr + 16 l.  Written as assembly so that the
+// buffer land at LDS byte lds_addr + Imm + 16 l.  Written as assembly so that the
 // compiler's wait insertion does not make every later LDS read wait for it;
 // completion is awaited explicitly (vm_wait) before the barrier that
 // publishes a tile.
+template <int Imm>
 __device__ __forceinline__ void lds_dma16(u32x4 r, uint32_t lds_addr, uint32_t voff) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+  asm volatile("s_add_u32 m0, %0, %3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                :
-               : "s"(lds_addr), "v"(voff), "s"(r)
-               : "memory", "m0");
+               : "s"(lds_addr), "v"(voff), "s"(r), "i"(Imm)
+               : "memory", "m0", "scc");
 }
 
 // s_waitcnt vmcnt(N), expcnt and lgkmcnt left open (gfx9 encoding).
@@ -106,16 +108,25 @@ __device__ __forceinline__ int4 scalar4(const int4 &v) {
                    __builtin_amdgcn_readfirstlane(v.z), __builtin_amdgcn_readfirstlane(v.w));
 }
 
+// x clamped to [0, hi] in scalar registers (x is the same in every lane; the
+// compiler would take the vector unit's three-way median).
+__device__ __forceinline__ uint32_t scalar_clamp(int x, int hi) {
+  uint32_t r;
+  asm("s_min_i32 %0, %1, %2\n\ts_max_i32 %0, %0, 0" : "=s"(r) : "s"(x), "s"(hi) : "scc");
+  return r;
+}
+
 // Closed-form plan of rows at q_pos0 + r: block pb's {maxpos, minpos, n_s,
-// chunk} (positions clamped to the cache, n_s near-equal splits).
+// chunk} (positions clamped to the cache, n_s near-equal splits).  Pair
+// indices stay below 2^20 (at most kAttnPlanMaxBlocks blocks).
 __device__ __forceinline__ int4 uniform_block_info(int pb, int ppb, int group, int n_rows, int q_pos0,
                                                    int n_ctx, int ns) {
-  const int64_t p0 = (int64_t)pb * ppb;
-  const int64_t p1 = min(p0 + ppb, (int64_t)n_rows * group) - 1;
-  const int minpos = min(q_pos0 + (int)(p0 / group), n_ctx - 1);
-  const int maxpos = min(q_pos0 + (int)(p1 / group), n_ctx - 1);
-  const int tiles = maxpos / KT + 1;
-  return make_int4(maxpos, minpos, ns, ((tiles + ns - 1) / ns) * KT);
+  const uint32_t p0 = (uint32_t)pb * ppb;
+  const uint32_t p1 = min(p0 + ppb, (uint32_t)n_rows * group) - 1;
+  const int minpos = min(q_pos0 + (int)(p0 / (uint32_t)group), n_ctx - 1);
+  const int maxpos = min(q_pos0 + (int)(p1 / (uint32_t)group), n_ctx - 1);
+  const uint32_t tiles = (uint32_t)maxpos / KT + 1;
+  return make_int4(maxpos, minpos, ns, (int)((tiles + ns - 1) / (uint32_t)ns) * KT);
 }
 
 
@@ -314,9 +325,11 @@ __global__ __launch_bounds__(kPlanThreads) void plan_scatter_kernel(PlanArgs a, 
   if (row < sp.n_rows) scatter_row(sp, row, threadIdx.x & 63);
 }
 
-// W waves per workgroup, each owning 32 (row, head) pair columns.  With
-// values (refresh) W = 8: two waves per SIMD and 256 pairs sharing each K/V
-// tile; statistics only W = 4 with two workgroups per CU.  The grid is
+// W waves per workgroup.  With values (refresh) W = 8, each wave owning 32
+// (row, head) pair columns: two waves per SIMD and 256 pairs sharing each K/V
+// tile.  Statistics only W = 4 with two workgroups per CU and 128 pairs: wave
+// w owns 64 columns (w mod 2) and one of every tile's two sub-tiles (w / 2),
+// so that each K operand read from LDS feeds two products.  The grid is
 // persistent: workgroup g takes items g, 2G' - 1 - g, 2G' + g, ... of the
 // plan (G' = grid size), i.e. snake order over a largest-first list.
 // ML: several layers per launch (LayerTable); item i of the launch is plan
@@ -327,12 +340,24 @@ template <int D, bool PV, int W, bool UNI, bool ML = false>
 __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, LayerTable lt) {
   constexpr int kThreads = W * 64;
   constexpr int kPairs = W * 32;  // (row, head) pairs per block
+  constexpr int NC = PV ? 1 : 2;  // 32-column blocks per wave
   constexpr int KS = D / 16;      // MFMA k-steps over the head dimension
   constexpr int DT = D / 32;      // 32-row tiles of O^T
   __shared__ AttnSmem<D, PV> sm;
   __shared__ int s_restart;  // attempt id of the item being restarted (see kHeadroom)
   __shared__ int s_last;     // statistics: this workgroup holds the last split of its block
 
+  // The parameter block is read in one go (otherwise each scalar is loaded
+  // where it is first used, a chain of round trips before the first tile).
+  asm volatile("" ::"s"(p.k), "s"(p.q), "s"(p.k_stride), "s"(p.pages.table), "s"(p.pages.shift), "s"(p.pages.n_pages),
+               "s"(p.n_kv_heads), "s"(p.group), "s"(p.n_q_heads), "s"(p.n_ctx), "s"(p.n_rows), "s"(p.row_pos),
+               "s"(p.q_pos0), "s"(p.scale_log2), "s"(p.plan.n_pb), "s"(p.plan.max_items), "s"(p.plan.uniform_ns),
+               "s"(p.plan.uniform_items), "s"(p.zero_i32), "s"(p.zero_n), "s"(p.row_b), "s"(p.lse_out));
+  if constexpr (PV)
+    asm volatile("" ::"s"(p.v), "s"(p.v_stride), "s"(p.o_out), "s"(p.part_o), "s"(p.plan.items), "s"(p.plan.pb_info),
+                 "s"(p.plan.hdr));
+  else
+    asm volatile("" ::"s"(p.part_m), "s"(p.part_l), "s"(p.merge_flag), "s"(p.epoch), "s"(p.vis_only));
   const int G = p.group;
   const int n_pairs = p.n_rows * G;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -361,36 +386,32 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
     const int row = (lrow & ~15) | v_interleaved_key(lrow & 15);
     return ch < D / 8 ? (uint32_t)row * (uint32_t)(2 * p.v_stride) + 16u * ch : kPadOff;
   };
-  // Wave w issues transfers w, w + W, ... of a K tile.  With values, tiles
-  // come in groups of two K and two V tiles: each wave takes transfers w,
-  // w + W, ... below the last whole multiple of W of every tile, and one of
-  // the group's left-over transfers (waves past the last one repeat it: the
-  // same bytes to the same place), so that every wave issues the same number
-  // with no branch.
-  constexpr int kFull = Geo::kXfer / W, vFull = Geo::vXfer / W;
-  constexpr int kLeft = Geo::kXfer % W, vLeft = Geo::vXfer % W;
-  constexpr int kSlots = PV ? kFull : (Geo::kXfer + W - 1) / W;
-  static_assert(!PV || 2 * (kLeft + vLeft) <= W, "one left-over transfer per wave");
-  uint32_t ko[kSlots], vo[PV ? vFull : 1], xo = 0;
+  // Tiles come in groups of two K and (with values) two V tiles: each wave
+  // takes transfers w, w + W, ... below the last whole multiple of W of every
+  // tile, and one of the group's left-over transfers (waves past the last one
+  // repeat it: the same bytes to the same place), so that every wave issues
+  // the same number with no branch.
+  constexpr int kFull = Geo::kXfer / W, vFull = PV ? Geo::vXfer / W : 0;
+  constexpr int kLeft = Geo::kXfer % W, vLeft = PV ? Geo::vXfer % W : 0;
+  constexpr int kLeftAll = 2 * (kLeft + vLeft);
+  static_assert(kLeft >= 1 && kLeftAll <= W, "one left-over transfer per wave");
+  uint32_t ko[kFull], vo[PV ? vFull : 1], xo;
 #pragma unroll
-  for (int sl = 0; sl < kSlots; ++sl) {
+  for (int sl = 0; sl < kFull; ++sl) {
     ko[sl] = k_off(wave + W * sl);
     asm volatile("" : "+v"(ko[sl]));  // one register each (else the division that formed it is kept as a pair)
   }
-  const int left = min(wave, 2 * (kLeft + vLeft) - 1);  // left-over transfer: Ka.., Kb.., Va.., Vb..
-  const int left_x = left < 2 * kLeft ? kFull * W + left % (kLeft > 0 ? kLeft : 1)
-                                      : vFull * W + (left - 2 * kLeft) % (vLeft > 0 ? vLeft : 1);
-  const bool left_k = left < 2 * kLeft;
-  const bool left_b = left_k ? left >= kLeft : left >= 2 * kLeft + vLeft;  // of the group's second tile
-  if constexpr (PV) {
 #pragma unroll
-    for (int sl = 0; sl < vFull; ++sl) {
-      vo[sl] = v_off(wave + W * sl);
-      asm volatile("" : "+v"(vo[sl]));
-    }
-    xo = left_k ? k_off(left_x) : v_off(left_x);
-    asm volatile("" : "+v"(xo));
+  for (int sl = 0; sl < vFull; ++sl) {
+    vo[sl] = v_off(wave + W * sl);
+    asm volatile("" : "+v"(vo[sl]));
   }
+  const int left = min(wave, kLeftAll - 1);  // left-over transfer: Ka.., Kb.., Va.., Vb..
+  const bool left_k = !PV || left < 2 * kLeft;
+  const int left_x = left_k ? kFull * W + left % kLeft : vFull * W + (left - 2 * kLeft) % (vLeft > 0 ? vLeft : 1);
+  const bool left_b = left_k ? left >= kLeft : left >= 2 * kLeft + vLeft;  // of the group's second tile
+  xo = left_k ? k_off(left_x) : v_off(left_x);
+  asm volatile("" : "+v"(xo));
   const u16 *Qg = static_cast<const u16 *>(p.q);
   void *o_out = p.o_out;
   float *lse_out = p.lse_out;
@@ -444,22 +465,8 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
     if (kbeg >= kend) continue;
     const int pair0 = pb * kPairs;
 
-    // The pair column owned by this lane.
-    const int pair = pair0 + wave * 32 + col;
-    const bool valid = pair < n_pairs;
-    const int r = valid ? pair / G : 0;
-    const int gpair = r * p.n_q_heads + kvh * G + (valid ? pair % G : 0);
-    const int rp = valid ? row_position(p.row_pos, p.q_pos0, r) : -1;
-    bf16x8 qreg[KS];
-    {
-      const u16 *qrow = Qg + (int64_t)gpair * D + 8 * half;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        qreg[ks] = as_bf16x8(valid ? ld16(qrow + ks * 16) : u32x4{0, 0, 0, 0});
-    }
-
     // Statistics only (visual-only domain): one bit per key of the tile at
-    // t0 in K stage st, set by wave 0 beside the tile's transfers.
+    // t0 (tile st of the item, mod 8), set by wave 0.
     auto okmask_tile = [&](int st, int t0) __attribute__((always_inline)) {
       if constexpr (!PV) {
         if (p.vis_only && wave == 0) {
@@ -480,45 +487,52 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
     const uint64_t k_base = (uint64_t)(uintptr_t)Kg + head_b, v_base = (uint64_t)(uintptr_t)Vg + head_b;
     auto tile_rsrc = [&](uint64_t base, uint32_t row_b, int t0, uint32_t row) __attribute__((always_inline)) {
       const uint64_t ga = base + (uint64_t)row * row_b;
-      const int rows = min(max(kend - t0, 0), KT);
+      const uint32_t rows = scalar_clamp(kend - t0, KT);
       u32x4 r;
       r[0] = __builtin_amdgcn_readfirstlane((uint32_t)ga);
       r[1] = __builtin_amdgcn_readfirstlane((uint32_t)(ga >> 32));
-      r[2] = __builtin_amdgcn_readfirstlane((uint32_t)max((int)(rows * row_b) - (int)head_b, 0));
+      r[2] = rows * row_b;
       r[3] = kRawBufferWord3;
       return r;
     };
-    auto k_stage = [&](int st) __attribute__((always_inline)) { return (uint32_t)(uintptr_t)&sm.k[st][0][0]; };
-    auto v_stage = [&](int st) __attribute__((always_inline)) { return (uint32_t)(uintptr_t)&sm.v[PV ? st : 0][0][0]; };
+    // LDS address of this wave's first transfer of a stage (its others sit
+    // W KB apart), and of the left-over transfers' first.
+    auto k_stage = [&](int st) __attribute__((always_inline)) {
+      return (uint32_t)(uintptr_t)&sm.k[st][0][0] + wave * 1024;
+    };
+    auto v_stage = [&](int st) __attribute__((always_inline)) {
+      return (uint32_t)(uintptr_t)&sm.v[PV ? st : 0][0][0] + wave * 1024;
+    };
     // This wave's transfers of the K tile at t0 into K stage st.
     auto dma_k = [&](int st, int t0, uint32_t row) __attribute__((always_inline)) {
       const u32x4 rs = tile_rsrc(k_base, k_row_b, t0, row);
-#pragma unroll
-      for (int sl = 0; sl < kSlots; ++sl)
-        if (PV || wave + W * sl < Geo::kXfer)
-          lds_dma16(rs, __builtin_amdgcn_readfirstlane(k_stage(st) + (wave + W * sl) * 1024), ko[sl]);
-      if constexpr (PV) {
-        if (wave < kLeft)
-          lds_dma16(rs, __builtin_amdgcn_readfirstlane(k_stage(st) + (kFull * W + wave) * 1024), xo);
-      }
+      const uint32_t base = k_stage(st);
+      auto one = [&](auto sl) __attribute__((always_inline)) {
+        if constexpr (decltype(sl)::value < kFull) lds_dma16<decltype(sl)::value * W * 1024>(rs, base, ko[decltype(sl)::value]);
+      };
+      one(std::integral_constant<int, 0>{});
+      one(std::integral_constant<int, 1>{});
+      one(std::integral_constant<int, 2>{});
+      one(std::integral_constant<int, 3>{});
+      static_assert(kFull <= 4, "every whole transfer issued");
+      if (wave < kLeft) lds_dma16<kFull * W * 1024>(rs, base, xo);
     };
-    // A group of transfers: K tiles into stages k0, k1 and V tiles into v0, v1.
+    // A group of transfers: K tiles into stages at k0s, k1s and V tiles at
+    // v0s, v1s (LDS addresses of this wave's first transfer of each).
     struct Group {
       u32x4 k0, k1, v0, v1;
+      uint32_t k0s, k1s, v0s, v1s;
     };
     constexpr int kGroupXfers = 2 * (kFull + vFull) + 1;  // per wave
     // Transfer n of this wave's share of a group.
-    auto dma_group = [&](const Group &gr, int sk0, int sk1, int sv0, int sv1, int n) __attribute__((always_inline)) {
-      if (n < 2 * vFull) {
-        lds_dma16(n & 1 ? gr.v1 : gr.v0,
-                  __builtin_amdgcn_readfirstlane(v_stage(n & 1 ? sv1 : sv0) + (wave + W * (n / 2)) * 1024),
-                  vo[PV ? n / 2 : 0]);
-      } else if (n < 2 * vFull + 2 * kFull) {
-        const int i = n - 2 * vFull;
-        lds_dma16(i & 1 ? gr.k1 : gr.k0,
-                  __builtin_amdgcn_readfirstlane(k_stage(i & 1 ? sk1 : sk0) + (wave + W * (i / 2)) * 1024),
-                  ko[i / 2]);
-      } else {
+    auto dma_group = [&](const Group &gr, auto n_tag) __attribute__((always_inline)) {
+      constexpr int n = decltype(n_tag)::value;
+      if constexpr (n < 2 * vFull) {
+        lds_dma16<n / 2 * W * 1024>(n & 1 ? gr.v1 : gr.v0, n & 1 ? gr.v1s : gr.v0s, vo[PV ? n / 2 : 0]);
+      } else if constexpr (n < 2 * vFull + 2 * kFull) {
+        constexpr int i = n - 2 * vFull;
+        lds_dma16<i / 2 * W * 1024>(i & 1 ? gr.k1 : gr.k0, i & 1 ? gr.k1s : gr.k0s, ko[i / 2]);
+      } else if constexpr (n == 2 * vFull + 2 * kFull) {
         u32x4 r;
 #pragma unroll
         for (int e = 0; e < 3; ++e) {
@@ -526,42 +540,155 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
           r[e] = left_b ? b : a;
         }
         r[3] = kRawBufferWord3;
-        const uint32_t a = left_k ? k_stage(sk0) : v_stage(sv0), b = left_k ? k_stage(sk1) : v_stage(sv1);
-        lds_dma16(r, __builtin_amdgcn_readfirstlane((left_b ? b : a) + left_x * 1024), xo);
+        const uint32_t a = left_k ? gr.k0s : gr.v0s, b = left_k ? gr.k1s : gr.v1s;
+        lds_dma16<0>(r, (left_b ? b : a) + (left_x - wave) * 1024, xo);
       }
     };
+    // The transfers due at slot g of an iteration: transfer n at slot n * Spread.
+    auto dma_slot = [&](const Group &gr, int g, auto spread_tag) __attribute__((always_inline)) {
+      constexpr int S = decltype(spread_tag)::value;
+      auto at = [&](auto n) __attribute__((always_inline)) {
+        if (g == decltype(n)::value * S) dma_group(gr, n);
+      };
+      at(std::integral_constant<int, 0>{});
+      at(std::integral_constant<int, 1>{});
+      at(std::integral_constant<int, 2>{});
+      at(std::integral_constant<int, 3>{});
+      at(std::integral_constant<int, 4>{});
+      at(std::integral_constant<int, 5>{});
+      at(std::integral_constant<int, 6>{});
+      at(std::integral_constant<int, 7>{});
+      at(std::integral_constant<int, 8>{});
+      static_assert(kGroupXfers <= 9, "every transfer issued");
+    };
+
+    // Block-table entries of 64 consecutive tiles are read at once, one per
+    // lane, and each tile takes its entry with a lane read; only every 64th
+    // tile waits for the table.
+    const bool paged = p.pages.table != nullptr;
+    int page_vec = 0, page_base = -64;
+    // Makes the entries of the tile at t0 and of the three after it available
+    // (a tile past kend may take any row: its resource is empty).
+    auto pages_for = [&](int t0) __attribute__((always_inline)) {
+      const int ti = t0 / KT;
+      if (paged && ti + 3 - page_base >= 64) {
+        page_base = ti;
+        page_vec = read_page(pr, (ti + lane) * KT);
+        vm_wait<0>();  // here, not before every lane read (the tile transfers are invisible to the compiler)
+      }
+    };
+    auto tile_row = [&](int t0) __attribute__((always_inline)) -> uint32_t {
+      if (!paged) return (uint32_t)t0;
+      const uint32_t pg = (uint32_t)min(max(__builtin_amdgcn_readlane(page_vec, t0 / KT - page_base), 0), pr.last_page);
+      return (pg << pr.shift) | ((uint32_t)t0 & ((1u << pr.shift) - 1u));
+    };
+
+    // The item's first tiles, issued before its queries are read (again after
+    // a restart).
+    auto first_tiles = [&]() __attribute__((always_inline)) {
+    page_base = -64;
+    if constexpr (PV) {
+      // K(0..2), V(0..1); tiles past kend arrive as zeros
+      pages_for(kbeg);
+      const uint32_t r0 = tile_row(kbeg), r1 = tile_row(kbeg + KT), r2 = tile_row(kbeg + 2 * KT);
+      Group g0;
+      g0.k0 = tile_rsrc(k_base, k_row_b, kbeg, r0);
+      g0.k1 = tile_rsrc(k_base, k_row_b, kbeg + KT, r1);
+      g0.v0 = tile_rsrc(v_base, v_row_b, kbeg, r0);
+      g0.v1 = tile_rsrc(v_base, v_row_b, kbeg + KT, r1);
+      g0.k0s = k_stage(0);
+      g0.k1s = k_stage(1);
+      g0.v0s = v_stage(0);
+      g0.v1s = v_stage(1);
+      // K(0) first (the even K transfers and a left-over one): the first
+      // products need only that
+      constexpr int kV = 2 * vFull;
+#pragma unroll
+      for (int n = kV; n < kV + 2 * kFull; n += 2) dma_slot(g0, n, std::integral_constant<int, 1>{});
+      dma_slot(g0, kGroupXfers - 1, std::integral_constant<int, 1>{});
+#pragma unroll
+      for (int n = kV + 1; n < kV + 2 * kFull; n += 2) dma_slot(g0, n, std::integral_constant<int, 1>{});
+#pragma unroll
+      for (int n = 0; n < kV; ++n) dma_slot(g0, n, std::integral_constant<int, 1>{});
+      dma_k(2, kbeg + 2 * KT, r2);
+    } else {
+      // K(0), K(1) (tiles past kend arrive as zeros); K(2), K(3) follow once
+      // these and the queries are there (next_tiles): the start of the grid
+      // is bound by what its workgroups fetch before their first products
+      pages_for(kbeg);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) dma_k(i, kbeg + i * KT, tile_row(kbeg + i * KT));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) okmask_tile(i, kbeg + i * KT);
+    }
+    };
+    auto next_tiles = [&]() __attribute__((always_inline)) {
+      if constexpr (!PV) {
+        vm_wait<0>();
+#pragma unroll
+        for (int i = 2; i < 4; ++i) dma_k(i, kbeg + i * KT, tile_row(kbeg + i * KT));
+      }
+    };
+    first_tiles();
+
+    // The pair columns owned by this lane, and (statistics) the sub-tile of
+    // every tile that its wave takes.
+    const int col0 = PV ? wave * 32 : (wave & 1) * 64;
+    const int wsub = PV ? 0 : wave >> 1;
+    bool valid[NC];
+    int gpair[NC], rp[NC];
+    bf16x8 qreg[NC][KS];
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) {
+      const int pair = pair0 + col0 + cb * 32 + col;
+      valid[cb] = pair < n_pairs;
+      const int pr = valid[cb] ? pair : 0;
+      const int r = (int)((uint32_t)pr / (uint32_t)G);
+      gpair[cb] = r * p.n_q_heads + kvh * G + (pr - r * G);
+      rp[cb] = valid[cb] ? row_position(p.row_pos, p.q_pos0, r) : -1;
+      const u16 *qrow = Qg + (int64_t)gpair[cb] * D + 8 * half;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        qreg[cb][ks] = as_bf16x8(valid[cb] ? ld16(qrow + ks * 16) : u32x4{0, 0, 0, 0});
+    }
 
     // Running maximum (log2 units) starts finite, so exp2(c*s - m) needs no
     // special case: masked logits are -inf and give 0; the first tile with a
     // visible key always moves m.
-    float m = kMInit, l = 0.f;
+    float m[NC], l[NC];
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) m[cb] = kMInit;
     f32x16 o[DT];
 
     // S^T of one 32-key sub-tile: K operands from LDS, 8 chained MFMAs.
-    auto scores = [&](int buf, int sub) __attribute__((always_inline)) {
+    auto scores = [&](f32x16 (&s)[NC], int buf, int sub) __attribute__((always_inline)) {
       bf16x8 ka[KS];
       const u16 *krow = &sm.k[buf][sub * 32 + col][8 * half];
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) ka[ks] = as_bf16x8(ld16(krow + ks * 16));
-      f32x16 sc = f32x16{};
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], qreg[ks], sc, 0, 0, 0);
-      return sc;
+      for (int cb = 0; cb < NC; ++cb) {
+        s[cb] = f32x16{};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          s[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], qreg[cb][ks], s[cb], 0, 0, 0);
+      }
     };
-    // Tiles that need a key filter: causal / split end, and the key domain.
-    auto tile_masked = [&](int t0) __attribute__((always_inline)) {
-      return (!PV && p.vis_only) || t0 + KT > kend || t0 + KT - 1 > minpos;
-    };
-    // Key filter of sub-tile `sub` of the tile at t0 (K buffer buf).
-    auto mask_sub = [&](f32x16 &sc, int buf, int t0, int sub) __attribute__((always_inline)) {
-      const int lim = min(kend - 1, rp) - t0 - 4 * half;  // last visible key of the tile, lane-relative
+    // Tiles that need a key filter: those past t0 = mask_after (causal / split
+    // end), all of them with the visual-only domain.
+    const int mask_after = !PV && p.vis_only ? -1 : min(kend - KT, minpos - (KT - 1));
+    auto tile_masked = [&](int t0) __attribute__((always_inline)) { return t0 > mask_after; };
+    // Key filter of sub-tile `sub` of the tile at t0 (tile `buf` of the item,
+    // mod 8) for a pair column whose row sits at `rpos`.
+    auto mask_sub = [&](f32x16 &sc, int rpos, int buf, int t0, int sub) __attribute__((always_inline)) {
+      const int lim = min(kend - 1, rpos) - t0 - 32 * sub - 4 * half;  // last visible key, lane-relative
       // key-domain filter (statistics of visual-only scoring): the tile's
       // bits from this lane's first key on
       uint64_t dom = ~0ull;
-      if constexpr (!PV) dom = (sm.okmask[buf] | (p.vis_only ? 0ull : ~0ull)) >> (4 * half);
+      if constexpr (!PV) dom = (sm.okmask[buf] | (p.vis_only ? 0ull : ~0ull)) >> (32 * sub + 4 * half);
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int kl = sub * 32 + 8 * (v >> 2) + (v & 3);  // + 4 * half
+        const int kl = 8 * (v >> 2) + (v & 3);  // + 32 * sub + 4 * half
         bool ok = kl <= lim;
         if constexpr (!PV) ok = ok & (((dom >> kl) & 1ull) != 0);
         sc[v] = ok ? sc[v] : kNegInf;
@@ -578,24 +705,6 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
     // sub-tiles: each sub-step issues the S^T products of the next sub-tile
     // while it exponentiates the current one (independent work in one
     // instruction stream, so the matrix core and the VALU overlap).
-    // Block-table entries of 64 consecutive tiles are read at once, one per
-    // lane, and each tile takes its entry with a lane read; only every 64th
-    // tile waits for the table.
-    int page_vec = 0, page_base = -64;
-    // Makes the entries of the tile at t0 and of the two after it available
-    // (a tile past kend may take any row: its resource is empty).
-    auto pages_for = [&](int t0) __attribute__((always_inline)) {
-      const int ti = t0 / KT;
-      if (ti + 2 - page_base >= 64) {
-        page_base = ti;
-        page_vec = read_page(pr, (ti + lane) * KT);
-        vm_wait<0>();  // here, not before every lane read (the tile transfers are invisible to the compiler)
-      }
-    };
-    auto tile_row = [&](int t0) __attribute__((always_inline)) {
-      return (uint32_t)page_row(pr, __builtin_amdgcn_readlane(page_vec, t0 / KT - page_base), t0);
-    };
-
     // With values, the probabilities of an item are taken against one
     // reference maximum per pair column, fixed for the item: the first
     // sub-tile's maximum (kMInit if none of its keys is visible: then no key
@@ -614,89 +723,42 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
     // often outside it, which a fixed reference would turn into restarts).
     constexpr float kHeadroom = 32.f;
     constexpr float kHeadroomSum = 4294967296.f;  // 2^kHeadroom
-    float m_seen = kMInit;
+    float m_seen = kMInit;  // (with values)
     bool over = false;
     for (int attempt = 0;; ++attempt) {
-    l = 0.f;
-    page_base = -64;
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) l[cb] = 0.f;
     // Statistics over every key of the causal range take a fixed reference
     // in their first attempt like the values path; after a restart, or with
     // the visual-only domain, they keep the online maximum.
     const bool fixed_ref = PV ? attempt == 0 : attempt == 0 && !p.vis_only;
-    if constexpr (!PV) m = kMInit;
+    if constexpr (!PV) m[0] = m[NC - 1] = kMInit;
     if constexpr (PV) {
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) o[dt] = f32x16{};
     }
+    if (attempt > 0) first_tiles();
     if constexpr (PV) {
-      // K(0..2), V(0..1); tiles past kend arrive as zeros
-      pages_for(kbeg);
-      const uint32_t r0 = tile_row(kbeg), r1 = tile_row(kbeg + KT), r2 = tile_row(kbeg + 2 * KT);
-      Group g0;
-      g0.k0 = tile_rsrc(k_base, k_row_b, kbeg, r0);
-      g0.k1 = tile_rsrc(k_base, k_row_b, kbeg + KT, r1);
-      g0.v0 = tile_rsrc(v_base, v_row_b, kbeg, r0);
-      g0.v1 = tile_rsrc(v_base, v_row_b, kbeg + KT, r1);
-#pragma unroll
-      for (int n = 0; n < kGroupXfers; ++n) dma_group(g0, 0, 1, 0, 1, n);
-      dma_k(2, kbeg + 2 * KT, r2);
-      vm_wait<0>();
+      vm_wait<2 * kFull + 2 * vFull>();  // K(0)
     } else {
-      // K(0..2); tiles past kend arrive as zeros
-      pages_for(kbeg);
-      const uint32_t r0 = tile_row(kbeg), r1 = tile_row(kbeg + KT), r2 = tile_row(kbeg + 2 * KT);
-      dma_k(0, kbeg, r0);
-      okmask_tile(0, kbeg);
-      dma_k(1, kbeg + KT, r1);
-      okmask_tile(1, kbeg + KT);
-      dma_k(2, kbeg + 2 * KT, r2);
-      okmask_tile(2, kbeg + 2 * KT);
-      vm_wait<0>();
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) asm volatile("" ::"v"(qreg[cb][ks]));  // read by here, ahead of K(2), K(3)
+      next_tiles();
     }
     __syncthreads();
-    f32x16 sa = scores(0, 0), sb;
+    f32x16 sa[NC], sb[NC];
+    scores(sa, 0, wsub);
     if (PV || fixed_ref) {
-      if (tile_masked(kbeg)) mask_sub(sa, 0, kbeg, 0);
-      m = fmaxf(fmaxf(sub_max(sa), m_seen), kMInit);
-      m_seen = m;
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb) {
+        if (tile_masked(kbeg)) mask_sub(sa[cb], rp[cb], 0, kbeg, wsub);
+        m[cb] = fmaxf(PV ? fmaxf(sub_max(sa[cb]), m_seen) : sub_max(sa[cb]), kMInit);
+      }
+      if constexpr (PV) m_seen = m[0];
       over = false;
     }
-    // One sub-step of the statistics.  cur holds S^T of the current sub-tile
-    // (sub-tile csub of the tile at ct0, K stage cbuf); the S^T products of
-    // the next sub-tile (K stage kbn, rows ksub*32..; after the last
-    // sub-tile: discarded) are issued into nxt.  The key filter of cur comes
-    // first, so everything after it is one basic block: the compiler then
-    // places the exponentials of cur among the matrix products of nxt instead
-    // of sinking them past a later branch.  exact_tag std::false_type (a
-    // first attempt with a fixed reference) only checks that the sub-tile's
-    // probabilities stay below 2^kHeadroom in sum, which any sub-tile
-    // exceeding the reference by more than kHeadroom violates;
-    // std::true_type keeps the online maximum.
-    auto sub_step = [&](auto exact_tag, f32x16 &cur, f32x16 &nxt, int kbn, int ksub, bool cur_masked, int cbuf,
-                        int ct0, int csub) __attribute__((always_inline)) {
-      constexpr bool kExact = decltype(exact_tag)::value;
-      if (cur_masked) mask_sub(cur, cbuf, ct0, csub);
-      nxt = scores(kbn, ksub);
-      float alpha = 1.f;
-      if constexpr (kExact) {
-        const float mx = sub_max(cur);
-        const bool grow = mx > m + kRescaleSlack;
-        alpha = grow ? fast_exp2(m - mx) : 1.f;
-        m = grow ? mx : m;
-      }
-      const float neg_m = -m;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) cur[v] = fast_exp2(fmaf(cur[v], c, neg_m));
-      float psum = 0.f;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) psum += cur[v];
-      if constexpr (!kExact) over = over || !(psum <= kHeadroomSum);  // inf included
-      l = !kExact ? l + psum : l * alpha + psum;
-      // l is needed only after the loop; this empty statement makes it (and
-      // so this sub-tile's exponentials) due here, so the compiler does not
-      // sink them past the next sub-step's key filter.
-      asm volatile("" ::"v"(l));
-    };
     const int gen = ++attempt_id;  // the workgroup's attempts in order (uniform, never repeats)
     bool restart = false;
     if constexpr (PV) {
@@ -723,13 +785,16 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
       // every few slots (in one go at the iteration's start they cost the
       // products about 3%), planned during the previous iteration's last
       // sub-step and awaited before the barrier.  A tile past kend arrives as
-      // zeros (its resource is empty) and is masked whole.
+      // zeros (its resource is empty); an odd last tile leaves out its pair's
+      // second half.
       constexpr int kPv = 2 * DT;       // products of a sub-step's O^T update
       static_assert(kPv == KS, "one operand ring serves both product chains");
       constexpr int kSlots2 = KS + kPv, kEps = 16 / kSlots2;
       bf16x8 ring[KS], pk[2];
 #pragma unroll
       for (int j = 0; j < KS; ++j) ring[j] = as_bf16x8(ld16(&sm.k[0][32 + col][8 * half] + j * 16));
+      vm_wait<0>();
+      __syncthreads();  // every tile is there, and every wave has read K(0): the first iteration refills its stage
       pk[0] = pk[1] = as_bf16x8(u32x4{0, 0, 0, 0});
       // cur: S^T(i); nxt: receives S^T(i+1) from the ring; K operands read:
       // stage kst, rows ksub * 32..; V operands: stage vst, rows vsub * 32..;
@@ -737,13 +802,13 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
       // transfers' part of slot j.
       auto pv_step = [&](bool masked, f32x16 &cur, f32x16 &nxt, int kst, int ksub, int vst, int vsub, int ct0,
                          int csub, auto hook) __attribute__((always_inline)) {
-        if (masked) mask_sub(cur, 0, ct0, csub);
+        if (masked) mask_sub(cur, rp[0], 0, ct0, csub);
         if (!fixed_ref) {
           const float mx = sub_max(cur);
           m_seen = fmaxf(m_seen, mx);
-          over = over || mx > m + kHeadroom;
+          over = over || mx > m[0] + kHeadroom;
         }
-        const float neg_m = -m;
+        const float neg_m = -m[0];
         const u16 *krow = &sm.k[kst][ksub * 32 + col][8 * half];
         const u16 *vrow = &sm.v[vst][vsub * 32][0] + v_lane;
         // probabilities of sub-tile i; fp32 row sum (the log-sum-exp output
@@ -765,7 +830,7 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
 #pragma unroll
         for (int j = 0; j < kSlots2; ++j) {
           if (j < KS) {
-            nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[j], qreg[j], j == 0 ? f32x16{} : nxt, 0, 0, 0);
+            nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[j], qreg[0][j], j == 0 ? f32x16{} : nxt, 0, 0, 0);
             if (j & 1) {
               ring[j] = v_operand_il<Geo::vPitch>(vrow + (j / DT) * 16 * Geo::vPitch + (j % DT) * 32);
               ring[j - 1] = v_operand_il<Geo::vPitch>(vrow + ((j - 1) / DT) * 16 * Geo::vPitch + ((j - 1) % DT) * 32);
@@ -797,8 +862,8 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
           __builtin_amdgcn_sched_barrier(0);
         }
         over = over || (fixed_ref && !(psum <= kHeadroomSum));  // inf included
-        l += psum;
-        asm volatile("" ::"v"(l));
+        l[0] += psum;
+        asm volatile("" ::"v"(l[0]));
         pk[0] = as_bf16x8(pn[0]);
         pk[1] = as_bf16x8(pn[1]);
       };
@@ -836,20 +901,27 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
         // kSpread slots between two transfers
         constexpr int kSpread = 2 * kSlots2 / (kGroupXfers + 1);
         static_assert(kSpread >= 1 && kSpread * kGroupXfers <= 2 * kSlots2, "every transfer has a slot");
+        gr.k0s = k_stage(k3);
+        gr.k1s = k_stage(ks);
+        gr.v0s = v_stage(v2);
+        gr.v1s = v_stage(v3);
         auto issue = [&](int g) __attribute__((always_inline)) {
-          if (g % kSpread == kSpread - 1 && g / kSpread < kGroupXfers) dma_group(gr, k3, ks, v2, v3, g / kSpread);
+          dma_slot(gr, g - (kSpread - 1), std::integral_constant<int, kSpread>{});
         };
-        pv_step(m0, sa, sb, k1, 0, vlast, 1, t0, 0,     // P(t,0)   | S(t,1)   | PV(t-1,1)
+        pv_step(m0, sa[0], sb[0], k1, 0, vlast, 1, t0, 0,     // P(t,0)   | S(t,1)   | PV(t-1,1)
                 [&](int j) __attribute__((always_inline)) { issue(j); });
-        pv_step(m0, sb, sa, k1, 1, vs, 0, t0, 1,        // P(t,1)   | S(t+1,0) | PV(t,0)
+        pv_step(m0, sb[0], sa[0], k1, 1, vs, 0, t0, 1,        // P(t,1)   | S(t+1,0) | PV(t,0)
                 [&](int j) __attribute__((always_inline)) { issue(kSlots2 + j); });
-        pv_step(m1, sa, sb, k2, 0, vs, 1, t0 + KT, 0,   // P(t+1,0) | S(t+1,1) | PV(t,1)
-                [&](int) __attribute__((always_inline)) {});
-        pv_step(m1, sb, sa, k2, 1, v1, 0, t0 + KT, 1,   // P(t+1,1) | S(t+2,0) | PV(t+1,0)
-                [&](int j) __attribute__((always_inline)) {
-                  if (j % kPlanStep == 0 && j / kPlanStep < kPlanParts) plan_part(j / kPlanStep, t0 + 2 * KT);
-                });
-        vlast = v1;
+        vlast = vs;
+        if (t0 + KT < kend) {
+          vlast = v1;
+          pv_step(m1, sa[0], sb[0], k2, 0, vs, 1, t0 + KT, 0,   // P(t+1,0) | S(t+1,1) | PV(t,1)
+                  [&](int) __attribute__((always_inline)) {});
+          pv_step(m1, sb[0], sa[0], k2, 1, v1, 0, t0 + KT, 1,   // P(t+1,1) | S(t+2,0) | PV(t+1,0)
+                  [&](int j) __attribute__((always_inline)) {
+                    if (j % kPlanStep == 0 && j / kPlanStep < kPlanParts) plan_part(j / kPlanStep, t0 + 2 * KT);
+                  });
+        }
         if (__ballot(over) != 0 && lane == 0) s_restart = gen;
         vm_wait<0>();
         __syncthreads();
@@ -867,66 +939,162 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
               v_operand_il<Geo::vPitch>(vrow + (jj / DT) * 16 * Geo::vPitch + (jj % DT) * 32), pk[jj / DT], o[jj % DT], 0, 0, 0);
       }
     } else {
-      // One tile per barrier, K stages mod 4: iteration t reads K(t) and
-      // K(t+1) while K(t+2) is complete and K(t+3) arrives.  Before the
-      // barrier a wave waits until at most kSlots of its transfers are
-      // outstanding: all of K(t+2)'s, so only K(t+3)'s may remain.  K(t+3)
-      // is issued only if iteration t+2 exists (the first to read it);
-      // otherwise the wave waits for all of its transfers.
-      auto tiles = [&](auto exact_tag) __attribute__((always_inline)) {
-      constexpr bool kExact = decltype(exact_tag)::value;
-      int t0 = kbeg, st = 0;  // K stage of tile t
-      for (;;) {
-        const bool more = t0 + KT < kend;
-        const bool need3 = t0 + 2 * KT < kend;  // iteration t+2 exists
-        const int st1 = (st + 1) & 3, st3 = (st + 3) & 3;
-        if (need3) {
-          pages_for(t0 + 3 * KT);
-          dma_k(st3, t0 + 3 * KT, tile_row(t0 + 3 * KT));
-          okmask_tile(st3, t0 + 3 * KT);
+      // Statistics: the same pipeline without the values' third, over the
+      // wave's sub-tile i of tile i.  A sub-step holds 2 KS slots, each one
+      // S^T product of sub-tile i + 1 and 16 / KS exponentials of sub-tile i,
+      // and leaves the K operands of sub-tile i + 2 in the ring.  The slots
+      // are bound by instruction issue: measured with interleaved probes at
+      // two waves per SIMD, a product with its 2 exponentials, 2 FMAs and 2
+      // additions takes 42 cycles (the product alone 32), an LDS read of one
+      // operand per product adds 13 and every 4 scalar operations about 10,
+      // so each operand read feeds two products here (64 columns per wave)
+      // and the scalar work is shared by 32 products.  Two tiles (t, t+1) per
+      // barrier: the iteration reads K(t+2) and K(t+3) while K(t+4) and
+      // K(t+5) arrive.
+      bf16x8 ring[KS];
+#pragma unroll
+      for (int j = 0; j < KS; ++j) ring[j] = as_bf16x8(ld16(&sm.k[1][32 * wsub + col][8 * half] + j * 16));
+      vm_wait<0>();
+      __syncthreads();  // K(2), K(3) are there, and every wave has read K(0), K(1): the first iteration refills their stages
+      constexpr int kEps = 16 / KS;
+      auto st_step = [&](bool masked, f32x16 (&cur)[NC], f32x16 (&nxt)[NC], int kst, int ok, int ct0,
+                         auto hook) __attribute__((always_inline)) {
+        if (masked) {
+#pragma unroll
+          for (int cb = 0; cb < NC; ++cb) mask_sub(cur[cb], rp[cb], ok, ct0, wsub);
         }
-        const bool m0 = tile_masked(t0);
-        sub_step(exact_tag, sa, sb, st, 1, m0, st, t0, 0);   // S(t,1)   | P(t,0)
-        sub_step(exact_tag, sb, sa, st1, 0, m0, st, t0, 1);  // S(t+1,0) | P(t,1)
-        if constexpr (!kExact) {
-          if (__ballot(over) != 0 && lane == 0) s_restart = gen;
+        if (!fixed_ref) {  // online maximum
+#pragma unroll
+          for (int cb = 0; cb < NC; ++cb) {
+            const float mx = sub_max(cur[cb]);
+            const bool grow = mx > m[cb] + kRescaleSlack;
+            l[cb] *= grow ? fast_exp2(m[cb] - mx) : 1.f;
+            m[cb] = grow ? mx : m[cb];
+          }
         }
-        if (need3) vm_wait<kSlots - 1>();
-        else vm_wait<0>();
-        __syncthreads();
-        if constexpr (!kExact) restart = __builtin_amdgcn_readfirstlane(s_restart) == gen;
-        if (!more || restart) break;
-        t0 += KT;
-        st = st1;
-      }
+        const u16 *krow = &sm.k[kst][32 * wsub + col][8 * half];
+        float pe[NC * 16];
+        float psum[NC] = {};
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < NC * KS; ++j) {
+          const int op = j / NC, cb = j % NC;
+          nxt[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[op], qreg[cb][op], op == 0 ? f32x16{} : nxt[cb], 0, 0, 0);
+          if (cb == NC - 1 && (op & 1)) {
+            ring[op] = as_bf16x8(ld16(krow + op * 16));
+            ring[op - 1] = as_bf16x8(ld16(krow + (op - 1) * 16));
+          }
+#pragma unroll
+          for (int e = j * kEps; e < (j + 1) * kEps; ++e) {
+            pe[e] = fast_exp2(fmaf(cur[e / 16][e % 16], c, -m[e / 16]));
+            asm volatile("" ::"v"(pe[e]));
+            if (e >= 1) {
+              psum[(e - 1) / 16] += pe[e - 1];
+              asm volatile("" ::"v"(psum[(e - 1) / 16]));
+            }
+          }
+          hook(j);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        psum[NC - 1] += pe[NC * 16 - 1];
+#pragma unroll
+        for (int cb = 0; cb < NC; ++cb) {
+          over = over || (fixed_ref && !(psum[cb] <= kHeadroomSum));  // inf included
+          l[cb] += psum[cb];
+          asm volatile("" ::"v"(l[cb]));
+        }
       };
-      if (fixed_ref) tiles(std::false_type{});
-      else tiles(std::true_type{});
-      vm_wait<0>();  // the last transfers (zero tiles) land before the stages are reused
+      int t0 = kbeg, ks = 0, ti = 0;  // stage of tile t; tile of the item
+      Group gr;
+      uint32_t r4, r5;
+      constexpr int kPlanParts = 3;
+      auto plan_part = [&](int part, int t) __attribute__((always_inline)) {
+        if (part == 0) {
+          pages_for(t + 4 * KT);
+          r4 = tile_row(t + 4 * KT);
+          r5 = tile_row(t + 5 * KT);
+        } else if (part == 1) {
+          gr.k0 = tile_rsrc(k_base, k_row_b, t + 4 * KT, r4);
+        } else {
+          gr.k1 = tile_rsrc(k_base, k_row_b, t + 5 * KT, r5);
+        }
+      };
+#pragma unroll
+      for (int i = 0; i < kPlanParts; ++i) plan_part(i, t0);
+      for (;;) {
+        const int k1 = (ks + 1) & 3, k2 = (ks + 2) & 3, k3 = (ks + 3) & 3;
+        const bool more2 = t0 + 2 * KT < kend;  // the next iteration exists
+        const bool m0 = tile_masked(t0), m1 = tile_masked(t0 + KT);
+        okmask_tile((ti + 4) & 7, t0 + 4 * KT);
+        okmask_tile((ti + 5) & 7, t0 + 5 * KT);
+        gr.k0s = k_stage(ks);
+        gr.k1s = k_stage(k1);
+        // slots of the iteration: a transfer every kSpread, then the next
+        // iteration's plan
+        constexpr int kIter = 2 * NC * KS, kSpread = kIter / (kGroupXfers + 1);
+        static_assert(kSpread * kGroupXfers + kPlanParts <= kIter, "everything has a slot");
+        auto slot = [&](int g) __attribute__((always_inline)) {
+          if (g < kSpread * kGroupXfers) {
+            dma_slot(gr, g, std::integral_constant<int, kSpread>{});
+          } else if (g - kSpread * kGroupXfers < kPlanParts) {
+            plan_part(g - kSpread * kGroupXfers, t0 + 2 * KT);
+          }
+        };
+        st_step(m0, sa, sb, k2, ti & 7, t0,  // P(t) | S(t+1)
+                [&](int j) __attribute__((always_inline)) { slot(j); });
+        if (t0 + KT < kend)
+          st_step(m1, sb, sa, k3, (ti + 1) & 7, t0 + KT,  // P(t+1) | S(t+2)
+                  [&](int j) __attribute__((always_inline)) { slot(NC * KS + j); });
+        if (__ballot(over) != 0 && lane == 0) s_restart = gen;
+        vm_wait<0>();
+        __syncthreads();
+        restart = __builtin_amdgcn_readfirstlane(s_restart) == gen;
+        if (!more2 || restart) break;
+        t0 += 2 * KT;
+        ks = k2;
+        ti += 2;
+      }
     }
 
     if (!restart) break;
     }  // attempts
 
     // ---- outputs: final values for a single-split block, else partials ----
-    const float l_tot = l + __shfl_xor(l, 32, 64);
-    if (valid) {
-      if (single) {
-        const float b = m + __log2f(l_tot);
-        if (half == 0) {
-          if (row_b) row_b[gpair] = b;
-          if (lse_out) lse_out[gpair] = b * kLn2;
+    float l_tot[NC];
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) l_tot[cb] = l[cb] + __shfl_xor(l[cb], 32, 64);
+    if constexpr (!PV) {
+      // The two sub-tiles' sums of a column: M = max, L = sum l 2^(m - M).
+      if (wsub == 1 && half == 0) {
+#pragma unroll
+        for (int cb = 0; cb < NC; ++cb) sm.ml[col0 + cb * 32 + col] = make_float2(m[cb], l_tot[cb]);
+      }
+      __syncthreads();
+      if (wsub == 0) {
+#pragma unroll
+        for (int cb = 0; cb < NC; ++cb) {
+          const float2 x = sm.ml[col0 + cb * 32 + col];
+          const float M = fmaxf(m[cb], x.x);  // finite: both start at kMInit
+          l_tot[cb] = l_tot[cb] * fast_exp2(m[cb] - M) + x.y * fast_exp2(x.x - M);
+          m[cb] = M;
         }
+      }
+    }
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) {
+      if (!valid[cb] || wsub != 0 || half != 0) continue;
+      if (single) {
+        const float b = m[cb] + __log2f(l_tot[cb]);
+        if (row_b) row_b[gpair[cb]] = b;
+        if (lse_out) lse_out[gpair[cb]] = b * kLn2;
       } else {
-        const int64_t idx2 = (item.w + slot_off) * kPairs + wave * 32 + col;
-        if (half == 0) {
-          if (!PV && p.merge_flag) {  // read by another workgroup of this kernel
-            store_coherent(p.part_m + idx2, m);
-            store_coherent(p.part_l + idx2, l_tot);
-          } else {
-            p.part_m[idx2] = m;
-            p.part_l[idx2] = l_tot;
-          }
+        const int64_t idx2 = (item.w + slot_off) * kPairs + col0 + cb * 32 + col;
+        if (!PV && p.merge_flag) {  // read by another workgroup of this kernel
+          store_coherent(p.part_m + idx2, m[cb]);
+          store_coherent(p.part_l + idx2, l_tot[cb]);
+        } else {
+          p.part_m[idx2] = m[cb];
+          p.part_l[idx2] = l_tot[cb];
         }
       }
     }
@@ -941,7 +1109,7 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
       asm volatile("" : "+v"(otid));
       static_assert(kPairs * Geo::kPitch <= (int)(sizeof(sm.k) / 2), "output rows fit the K stages");
       u16 *orow = &sm.k[0][0][0];
-      const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+      const float inv = l_tot[0] > 0.f ? 1.f / l_tot[0] : 0.f;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -1003,7 +1171,9 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
             if (pair >= n_pairs) continue;
             const int gp = (pair / G) * p.n_q_heads + kvh * G + pair % G;
             // kMergeLoads splits' partials are loaded at once (indices
-            // clamped, so every load is issued), then reduced in order
+            // clamped, so every load is issued) and folded in order into a
+            // running maximum; up to kMergeLoads splits the sums are those
+            // of the two-pass formula.
             auto ld = [&](const float *a, int sp) __attribute__((always_inline)) {
               return __hip_atomic_load(a + (slot0 + min(sp, ns - 1)) * kPairs + j, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
@@ -1012,17 +1182,15 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
             float M = kNegInf, L = 0.f;
             for (int s0 = 0; s0 < ns; s0 += kMergeLoads) {
 #pragma unroll
-              for (int i = 0; i < kMergeLoads; ++i) mv[i] = ld(p.part_m, s0 + i);
-#pragma unroll
-              for (int i = 0; i < kMergeLoads; ++i) M = s0 + i < ns ? fmaxf(M, mv[i]) : M;
-            }
-            for (int s0 = 0; s0 < ns; s0 += kMergeLoads) {
-              if (ns > kMergeLoads) {  // else the one batch is still in registers
-#pragma unroll
-                for (int i = 0; i < kMergeLoads; ++i) mv[i] = ld(p.part_m, s0 + i);
+              for (int i = 0; i < kMergeLoads; ++i) {
+                mv[i] = ld(p.part_m, s0 + i);
+                lv[i] = ld(p.part_l, s0 + i);
               }
+              float Mn = M;
 #pragma unroll
-              for (int i = 0; i < kMergeLoads; ++i) lv[i] = ld(p.part_l, s0 + i);
+              for (int i = 0; i < kMergeLoads; ++i) Mn = s0 + i < ns ? fmaxf(Mn, mv[i]) : Mn;
+              L *= fast_exp2(M - Mn);  // 0 on the first batch
+              M = Mn;
 #pragma unroll
               for (int i = 0; i < kMergeLoads; ++i) L = s0 + i < ns ? L + fast_exp2(mv[i] - M) * lv[i] : L;
             }

@@ -97,12 +97,6 @@ __device__ __forceinline__ float half_max(float x) {
   return fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
 }
 
-__device__ __forceinline__ float half_sum(float x) {
-  const uint32_t u = __builtin_bit_cast(uint32_t, x);
-  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
-}
-
 __device__ __forceinline__ float wave_max(float x) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
@@ -170,12 +164,6 @@ __device__ __forceinline__ int read_page(const KvPageReader &r, int t) {
   return __builtin_amdgcn_raw_buffer_load_b32(r.rsrc, (t >> r.shift) * 4, 0, 0);
 }
 
-// Cache row of token t from its raw page entry.
-__device__ __forceinline__ int64_t page_row(const KvPageReader &r, int page, int t) {
-  const int pg = min(max(page, 0), r.last_page);
-  return ((int64_t)pg << r.shift) | (int64_t)((uint32_t)t & ((1u << r.shift) - 1u));
-}
-
 // The A operand of O^T += V^T P^T for one 16-key MFMA step, read from the
 // row-major V tile with two transposing LDS reads (ds_read_b64_tr_b16): in
 // each group of 16 lanes, lane 4j + q reads 4 head dims of key j and lane
@@ -186,22 +174,6 @@ typedef short short4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4 lds_short4;
 
 typedef short short8 __attribute__((ext_vector_type(8)));
-
-// Element offset, inside a V tile with row stride VS, of the 4 dims this
-// lane reads for the first half of an MFMA step (keys 0..7); the second
-// half (keys 8..15) is 8 rows further.
-template <int VS>
-__device__ __forceinline__ int v_operand_lane_offset(int lane) {
-  const int s = lane & 15, h = lane >> 5, dgrp = (lane >> 4) & 1;
-  return (4 * h + (s >> 2)) * VS + 16 * dgrp + 4 * (s & 3);
-}
-
-template <int VS>
-__device__ __forceinline__ bf16x8 v_operand(const u16 *at) {
-  const short4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)(at));
-  const short4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)(at + 8 * VS));
-  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
 
 // Interleaved V tile: key 8a + 4b + c of every 16-key block (a, b in {0, 1},
 // c in 0..3) is stored in row 8b + 2c + a of the block.  The four rows that
@@ -336,8 +308,9 @@ struct AttnParams {
   // Statistics with the closed-form plan (nullable): one mark per partial
   // slot, set to the call's epoch by the item that wrote the slot; the item
   // that finds every split of its block marked merges the block into
-  // row_b / lse_out.  Marks of another epoch count as unset, so they need no
-  // clearing.
+  // row_b / lse_out.  Marks of another epoch count as unset; the column sums
+  // that follow clear them, so that a captured launch, which replays one
+  // epoch, starts without marks too.
   uint32_t *merge_flag;
   uint32_t epoch;
 };
@@ -454,20 +427,14 @@ struct ColsumParams {
   float *colsum_part;       // [n_kv_heads][n_vis]: sum of alpha (or alpha^2 for RMS)
   float *vsq_part;          // [n_kv_heads][n_vis]
   const float *vnorm_in;    // nullable: value norms given, V not read
-  // Row log-sum-exp rebuilt from the statistics pass's split partials (its
-  // closed-form plan: lse_ns <= kLseRegSplits splits of lse_ppb-pair blocks)
-  // instead of read from row_b; the first key block also writes lse_out
-  // (natural log).
-  const float *lse_part_m;
-  const float *lse_part_l;
-  int32_t lse_ns;
-  int32_t lse_ppb;
-  float *lse_out;
-  int64_t lse_layer_stride;  // several layers: statistics partial slots per layer
   // fp32: the statistics' key splits ({m, l} per pair, lse_ns of them),
   // merged here instead of read from row_b (the first key block writes
   // lse_out).
   const float2 *f32_ml;
+  int32_t lse_ns;
+  float *lse_out;           // natural log
+  uint32_t *clear_u32;      // nullable: [clear_n] words cleared by the kernel (bf16)
+  int32_t clear_n;
   // nullable: arrival counters, one per key block, cleared beforehand; the
   // last KV head's workgroup of a key block finalizes its keys (fin).
   int32_t *done;
@@ -683,14 +650,6 @@ constexpr int64_t attn_max_items(int64_t n_pb, int64_t n_kv_heads, bool with_val
 }
 constexpr int kAttnKeyTile = 64;         // keys per LDS tile
 constexpr int64_t kMaxStrideBytes = int64_t(1) << 25;  // row strides below 32 MiB: a key tile spans < 2 GiB
-constexpr int kColsumKeysPerBlock = 256;  // visual keys per workgroup
-// Split statistics rows are merged by every column-sum workgroup (in LDS,
-// from registers) when the span has at most kColsumMaxLsePairs pairs per KV
-// head, at most kLseRegSplits splits and at most kColsumFuseMaxBlocks key
-// blocks (so few workgroups repeat it); otherwise the statistics kernel
-// merges them once.
-constexpr int kColsumMaxLsePairs = 4096;
-constexpr int kLseRegSplits = 24;
-constexpr int kColsumFuseMaxBlocks = 64;
+constexpr int kColsumKeysPerBlock = 256;  // visual keys per finalized block
 
 }  // namespace conduit

@@ -22,14 +22,6 @@ namespace {
 
 constexpr float kInf = __builtin_inff();
 
-constexpr int kColsumThreads = 512;   // 8 waves x 32 keys
-
-// Q rows stream through LDS in chunks of kQChunk (span token, head) rows,
-// double-buffered: the next chunk's global loads (unconditional, clamped
-// addresses) are in flight while the current chunk's kQChunk / 32 MFMA row
-// tiles and exponentials run, one barrier per chunk.  The V rows for the
-// value norms are fetched during the last chunk and consumed at the end.
-constexpr int kQChunk = 256;
 
 // Finalize of one visual token: fixed-order sum over KV heads, the mean (or
 // RMS) over rows and heads, the value norm, s = a v and the layer
@@ -121,20 +113,72 @@ __device__ __forceinline__ void finalize_when_last(const ColsumParams &p, const 
   }
 }
 
-// RMS: accumulate alpha^2 (Eq. 4's surrogate) instead of alpha.
-// FUSE: the row log-sum-exps are rebuilt from the statistics partials into
-// LDS (the split merge of the statistics pass, same order and arithmetic).
-// lt.n > 0: several layers, layer blockIdx.z (the statistics partials, column
-// sums and norms of layer l sit l strides further on).
-template <int D, bool RMS, bool FUSE>
-__global__ __launch_bounds__(kColsumThreads) void colsum_bf16_kernel(ColsumParams p, LayerTable lt) {
+// One 1 KB direct-to-LDS transfer through a buffer resource (lane l's 16 bytes
+// at byte voff land at LDS byte lds_addr + Imm + 16 l), written as assembly so
+// that the compiler does not make every later LDS read wait for it, awaited by
+// hand before the barrier that publishes it.
+template <int Imm>
+__device__ __forceinline__ void lds_dma16(__amdgpu_buffer_rsrc_t r, uint32_t lds_addr, uint32_t voff) {
+  asm volatile("s_add_u32 m0, %0, %3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+               :
+               : "s"(lds_addr), "v"(voff), "s"(r), "i"(Imm)
+               : "memory", "m0", "scc");
+}
+
+// The streamed rows' tiles: kQTile (span token, head) rows, D + 8 elements
+// apart (the lanes of an operand read cover distinct banks), a whole number of
+// 1 KB transfers.
+constexpr int kQTile = 64;
+constexpr int kQStages = 4;
+constexpr int kBTiles = 8;
+template <int D>
+struct ColsumSmem {
+  alignas(16) u16 q[kQStages][kQTile][D + 8];
+  alignas(16) float nb[kBTiles][kQTile];  // -b of the tiles' rows (doubled for RMS; past the last row: -inf)
+  uint32_t off[kBTiles][kQTile];          // byte offsets of the tiles' rows
+  int64_t row[kColsumKeysPerBlock];       // cache row of each key of the workgroup
+  float part[kColsumKeysPerBlock];        // RH = 2: column sums of the odd row halves
+  ImageLds img;
+};
+
+// RMS: accumulate alpha^2 = 2^(2 (c z - b)) (Eq. 4's surrogate) instead of
+// alpha: the scale and b are doubled (exact).
+// lt.n > 0: several layers, layer blockIdx.z (the column sums and norms of
+// layer l sit l strides further on).
+//
+// A workgroup covers 256 keys; every wave holds the K rows of 64 of them, so
+// that each Q operand read from LDS feeds two products.  RH = 1: 4 waves, each
+// takes every row, two workgroups per CU, so that one's start and end (K rows,
+// norms, the finalize handoff: about 8 us against 25 of the loop at 1,792
+// rows) run beside the other's loop.  RH = 2 (launches whose workgroups do not
+// fill the chip twice): 8 waves, wave w takes the 32-row half w / 4 of every
+// tile.  The loop runs over 32-row sub-tiles i with one product per slot:
+// S(i+1) = Q K^T from the operand ring while 2^(c S(i) - b) is summed on the
+// VALU and the ring receives the operands of i + 2.  It is bound by
+// instruction issue (a product with 2 exponentials, 2 FMAs and 2 additions
+// takes 42 cycles at two waves per SIMD, each LDS read about 13 more, the
+// product alone 32): 66 cycles per product over the whole kernel at 65,536
+// keys x 1,792 rows x 4 layers (0.94 M; 1.40 M with 32 keys per wave, operands
+// read one product ahead and one 8-wave workgroup per CU).
+template <int D, int RH>
+__global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumParams p, LayerTable lt, int rms) {
   constexpr int KS = D / 16;
+  constexpr int kThreads = 256 * RH, W = kThreads / 64;
+  // The parameter block is read in one go: the empty statement makes every
+  // scalar due here, otherwise each is loaded where it is first used, a chain
+  // of about a dozen round trips before the first product.  The image table's
+  // entries are on their way meanwhile.
+  const int tid = threadIdx.x;
+  const int img_off = p.tbl.off[min(tid, kMaxImages - 1)], img_pos = p.tbl.pos[min(tid, kMaxImages - 1)];
+  asm volatile("" ::"s"(p.k), "s"(p.v), "s"(p.q), "s"(p.row_b), "s"(p.vnorm_in), "s"(p.colsum_part), "s"(p.vsq_part),
+               "s"(p.k_stride), "s"(p.v_stride), "s"(p.pages.table), "s"(p.pages.shift), "s"(p.pages.n_pages),
+               "s"(p.n_kv_heads), "s"(p.group), "s"(p.n_q_heads), "s"(p.n_q), "s"(p.n_vis), "s"(p.scale_log2),
+               "s"(p.clear_u32), "s"(p.clear_n), "s"(p.done), "s"(p.tbl.n_images), "s"(lt.n));
   // This layer's pointers, in locals: p itself stays unwritten (a written
   // kernel parameter holding the image table would be copied to scratch).
   const bool ml = lt.n > 0;
   const int layer = ml ? (int)blockIdx.z : 0;
   const int64_t part_off = (int64_t)layer * p.n_kv_heads * p.n_vis;
-  const int64_t lse_off = p.lse_part_m ? layer * p.lse_layer_stride : 0;
   const void *k_l = ml ? layer_entry(lt.k, layer) : p.k;
   const void *v_l = ml ? layer_entry(lt.v, layer) : p.v;
   const void *q_l = ml ? layer_entry(lt.q, layer) : p.q;
@@ -142,275 +186,339 @@ __global__ __launch_bounds__(kColsumThreads) void colsum_bf16_kernel(ColsumParam
   const float *vnorm_in = ml ? layer_entry(lt.vnorm, layer) : p.vnorm_in;
   float *colsum_part = p.colsum_part + part_off;
   float *vsq_part = p.vsq_part + part_off;
-  const float *lse_part_m = p.lse_part_m ? p.lse_part_m + lse_off : nullptr;
-  const float *lse_part_l = p.lse_part_m ? p.lse_part_l + lse_off : nullptr;
-  float *lse_out = ml ? nullptr : p.lse_out;
-  constexpr int QCH = kQChunk * D / 8;       // 16-byte chunks in a Q chunk
-  constexpr int CPT = QCH / kColsumThreads;  // per thread
-  constexpr int VPT = kColsumKeysPerBlock * D / 8 / kColsumThreads;  // V chunks per thread
-  static_assert(QCH % kColsumThreads == 0, "Q chunk split");
-  __shared__ alignas(16) u16 qs[2][kQChunk][D + 8];
-  __shared__ alignas(16) float bs[2][kQChunk];
-  __shared__ ImageLds img;
-  __shared__ float b_all[FUSE ? kColsumMaxLsePairs : 1];
-  __shared__ int64_t s_row[kColsumKeysPerBlock];  // cache row of each key of the block
+  __shared__ ColsumSmem<D> sm;
+  float *const nb = &sm.nb[0][0];
 
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int col = lane & 31, half = lane >> 5;
+  const int key0 = (wave & 3) * 64, wsub = wave >> 2;
+  const int blk_key0 = blockIdx.x * kColsumKeysPerBlock;
   const int kvh = blockIdx.y;
   const int G = p.group;
   const int n_pair = p.n_q * G;
-  const int nch = (n_pair + kQChunk - 1) / kQChunk;
+  const int n_tiles = (n_pair + kQTile - 1) / kQTile;
+  const float b_scale = rms ? -2.f : -1.f;
+  const float c = rms ? 2.f * p.scale_log2 : p.scale_log2;
   const u16 *Kg = static_cast<const u16 *>(k_l);
   const u16 *Vg = static_cast<const u16 *>(v_l);
   const u16 *Qg = static_cast<const u16 *>(q_l);
+  // the statistics' merge marks, all read by now: unset for the next launch
+  if (p.clear_u32)
+    for (int i = ((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * kThreads + tid;
+         i < p.clear_n; i += gridDim.x * gridDim.y * gridDim.z * kThreads)
+      p.clear_u32[i] = 0;
 
-  // Chunk c into registers.  Item i of a thread is pair row
-  // c * kQChunk + tid / (D/8) + i * kRowStep, i.e. span row qq[i] and head
-  // rr[i] of the group (pair = qq * G + rr), kept from chunk to chunk by
-  // adding kQChunk = q_step * G + r_step.  The loads go through a buffer
-  // resource bounded by the span's queries, so rows past n_pair read as
-  // zeros (and their b as +inf when stored).
-  constexpr int kRowStep = kColsumThreads / (D / 8);
-  const int q_step = kQChunk / G, r_step = kQChunk % G;
-  int qq[CPT], rr[CPT];
-#pragma unroll
-  for (int i = 0; i < CPT; ++i) {
-    const int pr0 = tid / (D / 8) + kRowStep * i;
-    qq[i] = pr0 / G;
-    rr[i] = pr0 % G;
-  }
-  int qb = tid / G, rb = tid % G;  // statistics row of this thread (tid < kQChunk)
-  const auto q_rsrc = buffer_rsrc(Qg, p.n_q * p.n_q_heads * D * 2);
-  const auto b_rsrc = buffer_rsrc(row_b, FUSE ? 0 : p.n_q * p.n_q_heads * 4);
-  const uint32_t lane_b = (tid % (D / 8)) * 16;
+  // Direct-to-LDS staging of Q tiles, two at a time: wave w takes transfers
+  // w, w + W, ... below the last whole multiple of W of each tile, and one
+  // left-over transfer (waves past the last repeat it: the same bytes to the
+  // same place).  Row r of the KV head is span token r / G, head r mod G of
+  // the group; each lane keeps the byte offset and the head of its row per
+  // transfer and advances them by two tiles at a time.  Rows past n_pair lie
+  // past the resource's bound and read as zeros (their 2^-inf adds nothing);
+  // lanes that land in a row's padding start past it.
+  constexpr int kPitchB = 2 * (D + 8);
+  constexpr int kXfer = kQTile * kPitchB / 1024;
+  static_assert(kXfer * 1024 == kQTile * kPitchB, "whole 1 KB transfers");
+  constexpr int kFull = kXfer / W, kLeft = kXfer % W, kGroup = 2 * kFull + 1;
+  static_assert(kLeft >= 1 && 2 * kLeft <= W, "one left-over transfer per wave");
+  const int left = min(wave, 2 * kLeft - 1), left_x = kFull * W + left % kLeft;
+  const bool left_b = left >= kLeft;  // of the second tile
+  const uint32_t head_step = (uint32_t)D * 2u, tok_step = (uint32_t)p.n_q_heads * D * 2u;
+  // Rows of two tiles at a time: their byte offsets from the KV head's first
+  // row and their -b, one row per thread below 2 kQTile, kept as (token, head)
+  // and advanced from pair to pair instead of being divided out; threads past
+  // those rows do the same without storing.  Offsets go through a ring over
+  // kBTiles tiles; transfer n of this lane reads its row's at off_at[n], and
+  // adds its place in the row, chunk[n] (padding lanes: past the resource).
+  const uint32_t r0 = tid & (2 * kQTile - 1);
+  uint32_t row_tok = r0 / (uint32_t)G, row_head = r0 - row_tok * G;
+  const uint32_t tok_adv = 2 * kQTile / (uint32_t)G, head_adv = 2 * kQTile % (uint32_t)G;
+  const auto b_rsrc = buffer_rsrc(row_b, p.n_q * p.n_q_heads * 4);
   auto next_rows = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      rr[i] += r_step;
-      qq[i] += q_step;
-      if (rr[i] >= G) {
-        rr[i] -= G;
-        ++qq[i];
-      }
-    }
-    rb += r_step;
-    qb += q_step;
-    if (rb >= G) {
-      rb -= G;
-      ++qb;
-    }
+    row_tok += tok_adv;
+    row_head += head_adv;
+    const bool wrap = row_head >= (uint32_t)G;
+    row_tok += wrap;
+    row_head -= wrap ? G : 0;
   };
-  auto load_chunk = [&](u32x4 (&qv)[CPT], float &bv) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < CPT; ++i)
-      qv[i] = buffer_ld16(q_rsrc, (uint32_t)((qq[i] * p.n_q_heads + kvh * G + rr[i]) * D) * 2u + lane_b);
-    if (!FUSE && tid < kQChunk)
-      bv = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                         b_rsrc, (uint32_t)(qb * p.n_q_heads + kvh * G + rb) * 4u, 0, 0));
+  auto load_b = [&]() __attribute__((always_inline)) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                         b_rsrc, (row_tok * p.n_q_heads + kvh * G + row_head) * 4u, 0, 0));
   };
-  auto store_chunk = [&](int c, int buf, const u32x4 (&qv)[CPT], float bv) __attribute__((always_inline)) {
+  auto row_off = [&]() __attribute__((always_inline)) { return row_tok * tok_step + (kvh * G + row_head) * head_step; };
+  auto neg_b = [&](float b, int r) __attribute__((always_inline)) { return r < n_pair ? b_scale * b : -kInf; };
+  uint32_t off_at[kGroup], chunk[kGroup];
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      const int cidx = tid + kColsumThreads * i;
-      st16(&qs[buf][cidx / (D / 8)][(cidx % (D / 8)) * 8], qv[i]);
-    }
-    if (tid < kQChunk) {
-      const int pr = c * kQChunk + tid;
-      bs[buf][tid] = pr < n_pair ? (FUSE ? b_all[pr] : bv) : kInf;  // 2^-inf = 0
-    }
-  };
-
-  u32x4 qv[CPT];
-  float bv = kInf;
-  load_chunk(qv, bv);
-
-  // FUSE: b = M + log2(sum_s l_s 2^(m_s - M)) over the splits of the row's
-  // block, s ascending, exactly as the statistics merge computes it.  The
-  // host fuses only up to kLseRegSplits splits: they are read in one pass
-  // (indices clamped, so every read is issued unconditionally) and reduced
-  // from registers, two rows per thread and pass (a second row past n_pair
-  // reads the last row instead and is not stored).  Split sp of a row sits
-  // sp * lse_ppb floats after split 0: a scalar offset of the load, the
-  // same for every lane.  The first pass's reads go out before the image
-  // table and the K rows: they hit in the cache the statistics kernel just
-  // wrote, and reads issued after the K rows would wait for them (the memory
-  // counter returns in order).
-  const int ns = p.lse_ns;
-  const auto m_rsrc = buffer_rsrc(lse_part_m, FUSE ? 0x7fffffff : 0);
-  const auto l_rsrc = buffer_rsrc(lse_part_l, FUSE ? 0x7fffffff : 0);
-  const uint32_t split_b = (uint32_t)p.lse_ppb * 4u;
-  float mv[FUSE ? 2 : 1][FUSE ? kLseRegSplits : 1], lv[FUSE ? 2 : 1][FUSE ? kLseRegSplits : 1];
-  // Spans of at most kLseFewSplits splits read only that many (the tag
-  // gives the count read); the rest read all kLseRegSplits, clamped.
-  constexpr int kLseFewSplits = 8;
-  const bool few_splits = ns <= kLseFewSplits;
-  auto lse_issue = [&](int pr0, auto nsm_tag) __attribute__((always_inline)) {
-    constexpr int NSM = decltype(nsm_tag)::value;
-    if constexpr (FUSE) {
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int pr = min(pr0 + u * kColsumThreads, n_pair - 1);
-        const int pb = pr / p.lse_ppb, j = pr % p.lse_ppb;
-        const int64_t slot0 = ((int64_t)pb * p.n_kv_heads + kvh) * ns;
-        const uint32_t row_b0 = (uint32_t)(slot0 * p.lse_ppb + j) * 4u;
-#pragma unroll
-        for (int sp = 0; sp < NSM; ++sp) {
-          const uint32_t so = (uint32_t)min(sp, ns - 1) * split_b;
-          mv[u][sp] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(m_rsrc, row_b0, so, 0));
-          lv[u][sp] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(l_rsrc, row_b0, so, 0));
-        }
-      }
-    }
-  };
-  auto lse_reduce = [&](int pr0, auto nsm_tag) __attribute__((always_inline)) {
-    constexpr int NSM = decltype(nsm_tag)::value;
-    if constexpr (FUSE) {
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int pr = pr0 + u * kColsumThreads;
-        float M = -kInf, L = 0.f;
-#pragma unroll
-        for (int sp = 0; sp < NSM; ++sp) M = sp < ns ? fmaxf(M, mv[u][sp]) : M;
-#pragma unroll
-        for (int sp = 0; sp < NSM; ++sp) L = sp < ns ? L + fast_exp2(mv[u][sp] - M) * lv[u][sp] : L;
-        const float b = M + __log2f(L);
-        if (pr < n_pair) {
-          b_all[pr] = b;
-          if (blockIdx.x == 0 && lse_out) lse_out[(pr / G) * p.n_q_heads + kvh * G + pr % G] = b * kLn2;
-        }
-      }
-    }
-  };
-  using FewTag = std::integral_constant<int, kLseFewSplits>;
-  using AllTag = std::integral_constant<int, kLseRegSplits>;
-  if (FUSE && n_pair > 0) {
-    if (few_splits) lse_issue(tid, FewTag{});
-    else lse_issue(tid, AllTag{});
+  for (int n = 0; n < kGroup; ++n) {
+    const int x = n < 2 * kFull ? wave + W * (n / 2) : left_x;
+    const int b = x * 1024 + 16 * lane, ch = (b % kPitchB) / 16;
+    off_at[n] = b / kPitchB;
+    chunk[n] = ch < D / 8 ? 16u * ch : 0x80000000u;
+    asm volatile("" : "+v"(off_at[n]), "+v"(chunk[n]));
   }
-
-  image_table_to_lds(p.tbl, img, tid, kColsumThreads);
-  __syncthreads();
-  // This lane's key column, held as the B operand for every row tile.
-  const int t = blockIdx.x * kColsumKeysPerBlock + wave * 32 + col;
-  const bool tvalid = t < p.n_vis;
-  bf16x8 kreg[KS];
-  {
-    // the key's cache row (page lookup included), also kept for the V rows
-    const int64_t row = kv_row(p.pages, vis_position(img, tvalid ? t : p.n_vis - 1));
-    if (half == 0) s_row[wave * 32 + col] = row;
-    const u16 *krow = Kg + row * p.k_stride + kvh * D + 8 * half;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) kreg[ks] = as_bf16x8(ld16(krow + ks * 16));
-  }
-  // V rows of the block's keys for the value norms, 16 bytes per item (not
-  // read when the norms are given).  They are loaded during the last Q
-  // chunk, so that they do not compete with the K rows and the first chunk
-  // for memory bandwidth at the start; their addresses are formed after the
-  // first chunk is staged, from the rows the K loads resolved.
-  const bool read_v = vnorm_in == nullptr;
-  u32x4 vv[VPT];
-  const u16 *vsrc[VPT];
-  auto load_v = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < VPT; ++i) vv[i] = read_v ? ld16(vsrc[i]) : u32x4{0, 0, 0, 0};
-  };
-  const int v_chunk = nch - 1;  // no chunk load (and wait) follows
-  if constexpr (FUSE) {
-    if (few_splits) {
-      if (n_pair > 0) lse_reduce(tid, FewTag{});
-      for (int pr0 = tid + 2 * kColsumThreads; pr0 < n_pair; pr0 += 2 * kColsumThreads) {
-        lse_issue(pr0, FewTag{});
-        lse_reduce(pr0, FewTag{});
-      }
+  const auto q_rsrc = buffer_rsrc(Qg, p.n_q * p.n_q_heads * D * 2);
+  const uint32_t q_lds = (uint32_t)(uintptr_t)&sm.q[0][0][0] + wave * 1024;
+  constexpr uint32_t kStageB = kQTile * kPitchB;
+  // Transfer n of a tile pair whose row offsets are at off_a and off_b, into
+  // the stages at LDS addresses s_a, s_b (this wave's first transfer).
+  auto dma_q = [&](auto n_tag, const uint32_t *off_a, const uint32_t *off_b, uint32_t s_a, uint32_t s_b)
+      __attribute__((always_inline)) {
+    constexpr int n = decltype(n_tag)::value;
+    if constexpr (n < 2 * kFull) {
+      lds_dma16<n / 2 * W * 1024>(q_rsrc, n & 1 ? s_b : s_a, (n & 1 ? off_b : off_a)[off_at[n]] + chunk[n]);
     } else {
-      if (n_pair > 0) lse_reduce(tid, AllTag{});
-      for (int pr0 = tid + 2 * kColsumThreads; pr0 < n_pair; pr0 += 2 * kColsumThreads) {
-        lse_issue(pr0, AllTag{});
-        lse_reduce(pr0, AllTag{});
-      }
+      lds_dma16<0>(q_rsrc, (left_b ? s_b : s_a) + (left_x - wave) * 1024, (left_b ? off_b : off_a)[off_at[n]] + chunk[n]);
     }
-    __syncthreads();
-  }
-  store_chunk(0, 0, qv, bv);
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < VPT; ++i) {
-    const int vi = tid + kColsumThreads * i;  // key vi / (D/8) of the block (rows past n_vis repeat the last)
-    vsrc[i] = Vg + s_row[vi / (D / 8)] * p.v_stride + kvh * D + (vi % (D / 8)) * 8;
-  }
-
-  float colsum = 0.f;
-  for (int c = 0; c < nch; ++c) {
-    const int buf = c & 1;
-    const bool more = c + 1 < nch;
-    if (more) {
-      next_rows();
-      load_chunk(qv, bv);
-    }
-    if (c == v_chunk) load_v();
-    const int rows = min(kQChunk, n_pair - c * kQChunk);
-    auto row_step = [&](int r0) __attribute__((always_inline)) {
-      f32x16 acc0 = f32x16{}, acc1 = f32x16{};
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8 a0 = as_bf16x8(ld16(&qs[buf][r0 + col][ks * 16 + 8 * half]));
-        const bf16x8 a1 = as_bf16x8(ld16(&qs[buf][r0 + 32 + col][ks * 16 + 8 * half]));
-        acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, kreg[ks], acc0, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, kreg[ks], acc1, 0, 0, 0);
-      }
-      // lane (col, half), register v holds row 8*(v/4) + 4*half + v%4 of its tile
-      float part0 = 0.f, part1 = 0.f;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 b0 = *reinterpret_cast<const f32x4 *>(&bs[buf][r0 + 8 * g + 4 * half]);
-        const f32x4 b1 = *reinterpret_cast<const f32x4 *>(&bs[buf][r0 + 32 + 8 * g + 4 * half]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          // alpha = 2^(c z - b); RMS sums alpha^2 = 2^(2 (c z - b))
-          const float z0 = fmaf(acc0[4 * g + i], p.scale_log2, -b0[i]);
-          const float z1 = fmaf(acc1[4 * g + i], p.scale_log2, -b1[i]);
-          part0 += fast_exp2(RMS ? 2.f * z0 : z0);
-          part1 += fast_exp2(RMS ? 2.f * z1 : z1);
-        }
-      }
-      colsum += part0 + part1;
+  };
+  auto each = [&](auto f) __attribute__((always_inline)) {  // f(n) for every transfer of the pair
+    auto one = [&](auto n) __attribute__((always_inline)) {
+      if constexpr (decltype(n)::value < kGroup) f(n);
     };
-    // A full chunk's row steps unrolled: one step's products are independent
-    // of the previous step's exponentials, so the two overlap.
-    if (rows == kQChunk) {
-#pragma unroll
-      for (int r0 = 0; r0 < kQChunk; r0 += 64) row_step(r0);
-    } else {
-      for (int r0 = 0; r0 < rows; r0 += 64) row_step(r0);
+    one(std::integral_constant<int, 0>{});
+    one(std::integral_constant<int, 1>{});
+    one(std::integral_constant<int, 2>{});
+    one(std::integral_constant<int, 3>{});
+    one(std::integral_constant<int, 4>{});
+    one(std::integral_constant<int, 5>{});
+    one(std::integral_constant<int, 6>{});
+    one(std::integral_constant<int, 7>{});
+    one(std::integral_constant<int, 8>{});
+    static_assert(kGroup <= 9, "every transfer");
+  };
+  // Offsets of tiles 0..5 and -b of tiles 0..3.  (Threads of the upper half
+  // hold the same rows as the lower half's: they take the odd pairs.)
+  // The loads of b stay in flight until the K rows have been asked for.
+  float b_first = 0.f;
+  {
+    if (wave == 2 || wave == 3) next_rows();
+    if (wave < 4) {
+      sm.off[0][tid] = row_off();
+      b_first = load_b();
     }
-    if (more) store_chunk(c + 1, buf ^ 1, qv, bv);
+    if (wave < 2) {  // to the rows of tiles 4 and 5
+      next_rows();
+      next_rows();
+      sm.off[4][tid] = row_off();
+    }
+  }
+  // The image table, before the transfers: a wait for it behind them would
+  // wait for them too.
+  static_assert(kThreads >= kMaxImages, "one image per thread");
+  if (tid < p.tbl.n_images) {
+    sm.img.off[tid] = img_off;
+    sm.img.pos[tid] = img_pos;
+  }
+  if (tid == 0) {
+    sm.img.off[p.tbl.n_images] = p.n_vis;
+    sm.img.n_images = p.tbl.n_images;
+  }
+  __syncthreads();
+  // tiles 0 and 1, and 2 (RH = 1: the first iteration takes 3) or 2 and 3
+  each([&](auto n) __attribute__((always_inline)) { dma_q(n, sm.off[0], sm.off[1], q_lds, q_lds + kStageB); });
+  each([&](auto n) __attribute__((always_inline)) {
+    if (RH == 2 || (decltype(n)::value < 2 * kFull ? decltype(n)::value % 2 == 0 : !left_b))
+      dma_q(n, sm.off[2], sm.off[3], q_lds + 2 * kStageB, q_lds + 3 * kStageB);
+  });
+
+  // This lane's key columns, held as the B operands for every row tile.
+  bf16x8 kreg[2][KS];
+  {
+    // the keys' cache rows (page lookup included), also kept for the V rows;
+    // both searches of the image table step together
+    int tk[2], lo[2] = {0, 0}, hi[2];
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) {
+      tk[cb] = min(blk_key0 + key0 + cb * 32 + col, p.n_vis - 1);
+      hi[cb] = sm.img.n_images - 1;
+    }
+    while (lo[0] < hi[0] || lo[1] < hi[1]) {
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) {
+        const int mid = (lo[cb] + hi[cb] + 1) >> 1;
+        const bool up = sm.img.off[mid] <= tk[cb];
+        lo[cb] = up ? mid : lo[cb];  // lo = hi stays: its offset is at most tk
+        hi[cb] = up ? hi[cb] : mid - 1;
+      }
+    }
+    int64_t row[2];
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+      row[cb] = kv_row(p.pages, sm.img.pos[lo[cb]] + (tk[cb] - sm.img.off[lo[cb]]));
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) {
+      if (half == 0 && wsub == 0) sm.row[key0 + cb * 32 + col] = row[cb];
+      const u16 *krow = Kg + row[cb] * p.k_stride + kvh * D + 8 * half;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kreg[cb][ks] = as_bf16x8(ld16(krow + ks * 16));
+    }
+  }
+  if (wave < 4) nb[tid] = neg_b(b_first, tid);
+  __builtin_amdgcn_s_waitcnt(0);  // this wave's Q transfers (invisible to the compiler)
+  __syncthreads();
+
+  // S of sub-tile 0, the operands of sub-tile 1 (RH = 2: of the next tile).
+  bf16x8 ring[KS];
+  f32x16 sa[2], sb[2];
+  {
+    const u16 *qrow = &sm.q[0][32 * wsub + col][8 * half];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) ring[ks] = as_bf16x8(ld16(qrow + ks * 16));
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) {
+      sa[cb] = f32x16{};
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        sa[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[ks], kreg[cb][ks], sa[cb], 0, 0, 0);
+    }
+    const u16 *qnext = RH == 1 ? qrow + 32 * (D + 8) : qrow + kQTile * (D + 8);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) ring[ks] = as_bf16x8(ld16(qnext + ks * 16));
+  }
+  __syncthreads();  // every wave has read these tiles: the first iteration refills their stages
+
+  float colsum[2] = {0.f, 0.f};
+  constexpr int kVPer = 16 / (2 * KS);  // accumulator registers (of both columns) per slot
+  // -b of the rows of sub-tile `sub` of a tile that this lane holds: register
+  // v of lane (col, half) is row 8*(v/4) + 4*half + v%4 of its sub-tile
+  auto b_of = [&](int tile, int sub) __attribute__((always_inline)) {
+    return nb + (tile & (kBTiles - 1)) * kQTile + 32 * sub + 4 * half;
+  };
+  f32x4 nb4 = *reinterpret_cast<const f32x4 *>(b_of(0, wsub));  // rows 0..3 of the current sub-tile
+  // One sub-step: cur = S(i), with b at bp; nxt receives S(i+1) from the
+  // ring, the ring rows qsub * 32.. of stage qst; bn: b of sub-tile i + 1.
+  auto step = [&](f32x16 (&cur)[2], f32x16 (&nxt)[2], int qst, int qsub, const float *bp, const float *bn,
+                  auto hook) __attribute__((always_inline)) {
+    const u16 *qrow = &sm.q[qst][32 * qsub + col][8 * half];
+    f32x4 nbn = nb4;
+    float last[2] = {0.f, 0.f}, psum[2] = {0.f, 0.f};
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < 2 * KS; ++j) {
+      const int op = j / 2, cb = j % 2;
+      nxt[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[op], kreg[cb][op], op == 0 ? f32x16{} : nxt[cb], 0, 0, 0);
+      if (cb == 1 && (op & 1)) {
+        ring[op] = as_bf16x8(ld16(qrow + op * 16));
+        ring[op - 1] = as_bf16x8(ld16(qrow + (op - 1) * 16));
+      }
+#pragma unroll
+      for (int v = j * kVPer; v < (j + 1) * kVPer; ++v) {
+        if (v % 4 == 0) {  // the next four rows' b, four registers ahead
+          nb4 = nbn;
+          nbn = *reinterpret_cast<const f32x4 *>(v < 12 ? bp + 8 * (v / 4 + 1) : bn);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const float pe = fast_exp2(fmaf(cur[u][v], c, nb4[v % 4]));
+          asm volatile("" ::"v"(pe));
+          psum[u] += last[u];
+          asm volatile("" ::"v"(psum[u]));
+          last[u] = pe;
+        }
+      }
+      hook(j);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    nb4 = nbn;
+    colsum[0] += psum[0] + last[0];
+    colsum[1] += psum[1] + last[1];
+    asm volatile("" ::"v"(colsum[0]), "v"(colsum[1]));
+  };
+  // Two tiles (t, t+1) per barrier.  RH = 1 reads tiles t+1, t+2 while t+3,
+  // t+4 arrive; RH = 2 (one sub-tile of each) reads t+2, t+3 while t+4, t+5
+  // arrive.
+  // V rows of the workgroup's keys for the value norms (not read when the
+  // norms are given), kVBatch 16-byte pieces per thread at a time; the first
+  // batch arrives during the last but one iteration.
+  const bool read_v = vnorm_in == nullptr;
+  constexpr int VPT = kColsumKeysPerBlock * D / 8 / kThreads, kVBatch = VPT < 8 ? VPT : 8;
+  u32x4 vv[kVBatch] = {};
+  auto load_v = [&](int i0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < kVBatch; ++i) {
+      const int vi = tid + kThreads * (i0 + i);
+      vv[i] = ld16(Vg + sm.row[vi / (D / 8)] * p.v_stride + kvh * D + (vi % (D / 8)) * 8);
+    }
+  };
+  const int v_at = max(((n_tiles - 1) & ~1) - 2, 0);
+  constexpr int kMod = kBTiles - 1;
+  for (int t = 0, st = 0; t < n_tiles; t += 2, st ^= 2) {
+    const int s1 = st + 1, s2 = st ^ 2, s3 = (st ^ 2) + 1;  // stages of t+1, t+2, t+3
+    constexpr int kStep = 2 * KS, kSpread = (RH == 1 ? 4 : 2) * kStep / kGroup;
+    static_assert(kSpread >= 1, "every transfer has a slot");
+    const uint32_t *off_a = sm.off[(t + 4) & kMod], *off_b = sm.off[(t + (RH == 1 ? 3 : 5)) & kMod];
+    const uint32_t s_a = q_lds + st * kStageB, s_b = q_lds + (RH == 1 ? s3 : s1) * kStageB;
+    auto slot = [&](int g) __attribute__((always_inline)) {
+      each([&](auto n) __attribute__((always_inline)) {
+        if (g == decltype(n)::value * kSpread) dma_q(n, off_a, off_b, s_a, s_b);
+      });
+    };
+    if (read_v && t == v_at) load_v(0);
+    // -b of the rows of tiles t+4, t+5 and the offsets of t+6, t+7
+    float bv = 0.f;
+    if (wave < 2) {
+      bv = load_b();
+      next_rows();
+      sm.off[(t + 6) & kMod][tid] = row_off();
+    }
+    if constexpr (RH == 1) {
+      step(sa, sb, s1, 0, b_of(t, 0), b_of(t, 1), [&](int j) __attribute__((always_inline)) { slot(j); });
+      step(sb, sa, s1, 1, b_of(t, 1), b_of(t + 1, 0), [&](int j) __attribute__((always_inline)) { slot(kStep + j); });
+      if (t + 1 < n_tiles) {
+        step(sa, sb, s2, 0, b_of(t + 1, 0), b_of(t + 1, 1),
+             [&](int j) __attribute__((always_inline)) { slot(2 * kStep + j); });
+        step(sb, sa, s2, 1, b_of(t + 1, 1), b_of(t + 2, 0),
+             [&](int j) __attribute__((always_inline)) { slot(3 * kStep + j); });
+      }
+    } else {
+      step(sa, sb, s2, wsub, b_of(t, wsub), b_of(t + 1, wsub), [&](int j) __attribute__((always_inline)) { slot(j); });
+      if (t + 1 < n_tiles)
+        step(sb, sa, s3, wsub, b_of(t + 1, wsub), b_of(t + 2, wsub),
+             [&](int j) __attribute__((always_inline)) { slot(kStep + j); });
+    }
+    if (wave < 2) sm.nb[(t + 4) & kMod][tid] = neg_b(bv, (t + 4) * kQTile + tid);
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's transfers have landed
     __syncthreads();
   }
-  colsum += __shfl_xor(colsum, 32, 64);
-  if (half == 0 && tvalid) store_coherent(colsum_part + (int64_t)kvh * p.n_vis + t, colsum);
+
+  // The lanes' halves of a key's rows, then (RH = 2) the row halves.
+#pragma unroll
+  for (int cb = 0; cb < 2; ++cb) {
+    colsum[cb] += __shfl_xor(colsum[cb], 32, 64);
+    if (RH == 2 && wsub == 1 && half == 0) sm.part[key0 + cb * 32 + col] = colsum[cb];
+  }
+  if (RH == 2) __syncthreads();
+  if (wsub == 0 && half == 0) {
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) {
+      const int i = key0 + cb * 32 + col, t = blk_key0 + i;
+      if (RH == 2) colsum[cb] += sm.part[i];
+      if (t < p.n_vis) store_coherent(colsum_part + (int64_t)kvh * p.n_vis + t, colsum[cb]);
+    }
+  }
 
   // Value-norm proxy: this head's share of ||V_t||^2.  Item vi covers
   // dims (vi % (D/8))*8 .. +7 of key vi / (D/8); the D/8 items of a key sit
   // in consecutive lanes and are summed with lane shuffles.
-  static_assert((D / 8) <= 64 && 64 % (D / 8) == 0, "key items within a wave");
+  static_assert((D / 8) <= 64 && 64 % (D / 8) == 0 && VPT % kVBatch == 0, "key items within a wave, whole batches");
+  for (int i0 = 0; read_v && i0 < VPT; i0 += kVBatch) {
+    if (i0 > 0) load_v(i0);
 #pragma unroll
-  for (int i = 0; read_v && i < VPT; ++i) {
-    float sq = 0.f;
+    for (int i = 0; i < kVBatch; ++i) {
+      float sq = 0.f;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float lo = __builtin_bit_cast(float, vv[i][e] << 16);
-      const float hi = __builtin_bit_cast(float, vv[i][e] & 0xffff0000u);
-      sq = fmaf(lo, lo, sq);
-      sq = fmaf(hi, hi, sq);
+      for (int e = 0; e < 4; ++e) {
+        const float lo = __builtin_bit_cast(float, vv[i][e] << 16);
+        const float hi = __builtin_bit_cast(float, vv[i][e] & 0xffff0000u);
+        sq = fmaf(lo, lo, sq);
+        sq = fmaf(hi, hi, sq);
+      }
+#pragma unroll
+      for (int o = 1; o < D / 8; o <<= 1) sq += __shfl_xor(sq, o, 64);
+      const int vi = tid + kThreads * (i0 + i), tv = blk_key0 + vi / (D / 8);
+      if (vi % (D / 8) == 0 && tv < p.n_vis) store_coherent(vsq_part + (int64_t)kvh * p.n_vis + tv, sq);
     }
-#pragma unroll
-    for (int o = 1; o < D / 8; o <<= 1) sq += __shfl_xor(sq, o, 64);
-    const int vi = tid + kColsumThreads * i;
-    const int tv = blockIdx.x * kColsumKeysPerBlock + vi / (D / 8);
-    if (vi % (D / 8) == 0 && tv < p.n_vis) store_coherent(vsq_part + (int64_t)kvh * p.n_vis + tv, sq);
   }
-  if (p.done) finalize_when_last(p, lt, tid, kColsumThreads);
+  if (p.done) finalize_when_last(p, lt, tid, kThreads);
 }
 
 // fp32 path: one wave per 64 visual keys of one KV head.  Lane j holds the
@@ -555,25 +663,18 @@ hipError_t launch_colsum(const ColsumParams &p, int head_dim, bool bf16, bool rm
                          const LayerTable *lt) {
   const LayerTable lt0 = lt ? *lt : LayerTable{};
   if (bf16) {
-    dim3 grid((p.n_vis + kColsumKeysPerBlock - 1) / kColsumKeysPerBlock, p.n_kv_heads, lt0.n > 0 ? lt0.n : 1);
+    const dim3 grid((p.n_vis + kColsumKeysPerBlock - 1) / kColsumKeysPerBlock, p.n_kv_heads, lt0.n > 0 ? lt0.n : 1);
+    // Two 4-wave workgroups per CU when the launch has that many, else 8-wave
+    // ones (4-layer document: 688 us with 8 waves, 573 with 4; one 16k layer,
+    // one workgroup per CU: 25 us with 8 waves, a wave per SIMD idles with 4).
+    const bool two = (int64_t)grid.x * grid.y * grid.z >= 512;
     ProfScope ps("colsum", s);
-    const bool fuse = p.lse_part_m != nullptr;
     if (head_dim == 128) {
-      if (fuse) {
-        if (rms) colsum_bf16_kernel<128, true, true><<<grid, kColsumThreads, 0, s>>>(p, lt0);
-        else colsum_bf16_kernel<128, false, true><<<grid, kColsumThreads, 0, s>>>(p, lt0);
-      } else {
-        if (rms) colsum_bf16_kernel<128, true, false><<<grid, kColsumThreads, 0, s>>>(p, lt0);
-        else colsum_bf16_kernel<128, false, false><<<grid, kColsumThreads, 0, s>>>(p, lt0);
-      }
+      if (two) colsum_bf16_kernel<128, 1><<<grid, 256, 0, s>>>(p, lt0, rms);
+      else colsum_bf16_kernel<128, 2><<<grid, 512, 0, s>>>(p, lt0, rms);
     } else {
-      if (fuse) {
-        if (rms) colsum_bf16_kernel<64, true, true><<<grid, kColsumThreads, 0, s>>>(p, lt0);
-        else colsum_bf16_kernel<64, false, true><<<grid, kColsumThreads, 0, s>>>(p, lt0);
-      } else {
-        if (rms) colsum_bf16_kernel<64, true, false><<<grid, kColsumThreads, 0, s>>>(p, lt0);
-        else colsum_bf16_kernel<64, false, false><<<grid, kColsumThreads, 0, s>>>(p, lt0);
-      }
+      if (two) colsum_bf16_kernel<64, 1><<<grid, 256, 0, s>>>(p, lt0, rms);
+      else colsum_bf16_kernel<64, 2><<<grid, 512, 0, s>>>(p, lt0, rms);
     }
   } else {
     dim3 grid((p.n_vis + 63) / 64, p.n_kv_heads);

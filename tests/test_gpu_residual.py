@@ -129,3 +129,23 @@ def test_residual_is_deterministic():
     mask = torch.zeros(w.n_vis, dtype=torch.uint8, device=DEV)
     z = to_dev(W.iso_directions(w, 0, M))
     assert np.array_equal(bits(run(w, kv, q, img, lse, mask, z)), bits(run(w, kv, q, img, lse, mask, z)))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_vis", [1, 63, 64, 65, 128, 129, 192, 2100])
+def test_residual_tile_pipeline(n_vis, d):
+    """Key ranges of one tile, of odd and even tile counts, whole and ragged, and of several splits: every stage of
+    the tile ring and of the sub-step pipeline is read and refilled."""
+    w = W.custom(1, 14, 2, d, 40, 3, [n_vis], 2, "bf16", n_sinks=min(2, n_vis), seed=n_vis + d)
+    L = w.layer(0, fresh=False)
+    k, v, q = (to_dev(L[x]) for x in ("k", "v", "q"))
+    kv = api.kv_desc(k, v, w.n_q_heads)
+    img = api.ImageTable(w.img_pos, w.img_off)
+    lse = row_lse(w, kv, q, img, O.NORM_CAUSAL_ROW)
+    mask = (np.arange(n_vis) % 5 == 3).astype(np.uint8)
+    for zs in (W.iso_directions(w, 0, 3), None):
+        got = run(w, kv, q, img, lse, torch.from_numpy(mask).to(DEV), None if zs is None else to_dev(zs))
+        xi = O.iso_displacements(L["v"], w.img_pos, w.img_off, zs, 0.5) if zs is not None else \
+            O.projected_displacements(L["v"], w.img_pos, w.img_off)
+        ref = O.residual_error(L["q"], L["k"], w.q_pos0, w.img_pos, w.img_off, mask, xi)
+        assert_scores(to_f64(got), ref, rtol=rtol(w), what="err")

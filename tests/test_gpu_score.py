@@ -193,3 +193,41 @@ def test_visual_only_statistics_far_below_a_text_key(boost):
         a, v, lse = O.score_layer(L.np["q"], L.np["k"], L.np["v"], w.q_pos0, w.img_pos, w.img_off, norm=norm)
         assert_scores(to_f64(got["a"]), a, what=f"a_t norm {norm}")
         assert_scores(to_f64(got["lse"]), lse, what=f"row lse norm {norm}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_q,hkv,g,images", [(1, 1, 1, [1]), (9, 2, 7, [255]), (64, 1, 1, [256]), (13, 2, 5, [200, 57]),
+                                              (32, 1, 4, [511, 2]), (43, 4, 3, [1000] * 3), (65, 2, 7, [2049]),
+                                              (7, 8, 7, [16384]), (43, 8, 3, [9000, 7500]), (90, 8, 7, [20000])])
+def test_score_tile_pipeline(d, n_q, hkv, g, images):
+    """Row counts around whole 64-row tiles (one tile, odd, even, ragged), key counts around whole 256-key
+    workgroups, and launches below and above 512 workgroups (one 8-wave or two 4-wave workgroups per CU): scores of
+    both aggregations against float64.  Products of bf16 inputs are exact; the fp32 sums of d of them and the
+    exponent's fp32 argument (below 64) leave less than 1e-4 relative, asserted at 2e-4."""
+    gen = torch.Generator(device=DEV).manual_seed(n_q * 17 + d)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device=DEV).to(torch.bfloat16)
+    img_pos, img_off, at = [], [0], 5
+    for n in images:
+        img_pos.append(at)
+        img_off.append(img_off[-1] + n)
+        at += n + 3
+    n_vis, q_pos0, n_ctx = img_off[-1], at, at + n_q
+    k, v, q = rnd(n_ctx, hkv, d), rnd(n_ctx, hkv, d), rnd(n_q, hkv * g, d)
+    img = api.ImageTable(np.array(img_pos, np.int32), np.array(img_off, np.int32))
+    vis = torch.cat([torch.arange(p, p + n, device=DEV) for p, n in zip(img_pos, images)])
+    ref = torch.zeros(2, n_vis, dtype=torch.float64, device=DEV)
+    hidden = torch.arange(n_ctx, device=DEV)[None] > q_pos0 + torch.arange(n_q, device=DEV)[:, None]
+    for h in range(hkv):
+        for j in range(g):
+            z = q[:, h * g + j].double() @ k[:, h].double().t() / d ** 0.5
+            alpha = torch.softmax(z.masked_fill(hidden, -torch.inf), dim=1)[:, vis]
+            ref += torch.stack([alpha.sum(0), (alpha ** 2).sum(0)])
+    ref /= n_q * hkv * g
+    ref[1].sqrt_()
+    vnorm = v[vis].double().flatten(1).norm(dim=1)
+    for r, agg in enumerate((api.AGG_MEAN, api.AGG_RMS)):
+        s, a, a_out = (torch.full((n_vis,), 7.0, device=DEV) for _ in range(3))
+        api.conduit_score(api.kv_desc(k, v, hkv * g), q, q_pos0, img, s, a, a_out=a_out, agg=agg)
+        assert float((a.double() / ref[r] - 1).abs().max()) < 2e-4
+        assert float((s.double() / (ref[r] * vnorm) - 1).abs().max()) < 2e-4
+        assert torch.equal(a, a_out)

@@ -31,6 +31,13 @@ uint32_t next_merge_epoch() {
   return e;
 }
 
+// Whether the column-sum workgroups merge the split statistics rows
+// themselves rather than the statistics kernel merging each block once.
+bool colsum_merges_lse(int32_t lse_ns, int64_t n_pair, int32_t n_vis, int32_t n_kv_heads, int32_t n_layers) {
+  return lse_ns > 1 && lse_ns <= kLseRegSplits && n_pair <= kColsumMaxLsePairs &&
+         colsum_blocks(n_vis, n_kv_heads, n_layers) < kColsumFourWaveBlocks;
+}
+
 namespace {
 
 thread_local std::string g_last_error;
@@ -386,6 +393,8 @@ conduit_status conduit_score(const conduit_kv *kv, const void *q, int32_t n_q, i
   float *row_b = reinterpret_cast<float *>(at(ws, L.row_b));
   const bool vis_only = norm == CONDUIT_NORM_VISUAL_ONLY;
 
+  int32_t lse_ns = 0;
+  bool merge_lse = false;
   DirectOut f32_stats{};  // fp32: the statistics' outputs (key splits merged by the column sums)
   hipError_t e;
   // bf16: the column-sum workgroups count their arrivals per key block and
@@ -424,10 +433,14 @@ conduit_status conduit_score(const conduit_kv *kv, const void *q, int32_t n_q, i
       ap.plan = plan_at(ws, L.plan);
       ap.part_m = reinterpret_cast<float *>(at(ws, L.plan.part_m));
       ap.part_l = reinterpret_cast<float *>(at(ws, L.plan.part_l));
-      // split rows: merged by the statistics kernel's last split of each
-      // block (no merge launch)
-      ap.merge_flag = reinterpret_cast<uint32_t *>(at(ws, L.merge_flag));
-      ap.epoch = next_merge_epoch();
+      // split rows: merged by the column-sum workgroups, or else by the
+      // statistics kernel's last split of each block (no merge launch)
+      lse_ns = attn_span_splits(ap, attn_pairs_per_block(false), 1);
+      merge_lse = colsum_merges_lse(lse_ns, (int64_t)n_q * ap.group, img->n_vis, kv->n_kv_heads, 1);
+      if (!merge_lse) {
+        ap.merge_flag = reinterpret_cast<uint32_t *>(at(ws, L.merge_flag));
+        ap.epoch = next_merge_epoch();
+      }
       ap.skip_merge = 1;
       ap.zero_i32 = done;
       ap.zero_n = n_done;
@@ -480,7 +493,13 @@ conduit_status conduit_score(const conduit_kv *kv, const void *q, int32_t n_q, i
     cs.lse_ns = f32_stats.n_split;
     cs.lse_out = row_lse_out;
   }
-  if (bf16 && !row_lse_in) {
+  if (merge_lse) {
+    cs.lse_part_m = reinterpret_cast<float *>(at(ws, L.plan.part_m));
+    cs.lse_part_l = reinterpret_cast<float *>(at(ws, L.plan.part_l));
+    cs.lse_ns = lse_ns;
+    cs.lse_ppb = attn_pairs_per_block(false);
+    cs.lse_out = row_lse_out;
+  } else if (bf16 && !row_lse_in) {
     cs.clear_u32 = reinterpret_cast<uint32_t *>(at(ws, L.merge_flag));
     cs.clear_n = L.plan.max_items;
   }
@@ -579,7 +598,7 @@ conduit_status conduit_score_layers(const conduit_kv *kvs, int32_t n_layers, con
   ap.plan = plan_at(ws, L.plan);
   ap.part_m = reinterpret_cast<float *>(at(ws, L.plan.part_m));
   ap.part_l = reinterpret_cast<float *>(at(ws, L.plan.part_l));
-  ap.skip_merge = 1;  // merged by the statistics kernel
+  ap.skip_merge = 1;  // merged by the column sums or by the statistics kernel (per launch, below)
   ap.zero_i32 = done;
   ap.zero_n = n_done;
 
@@ -625,11 +644,19 @@ conduit_status conduit_score_layers(const conduit_kv *kvs, int32_t n_layers, con
       lt.rowb[i] = row_b + i * rows;
       lt.vnorm[i] = vnorm_in ? vnorm_in[l0 + i] : nullptr;
     }
-    // the statistics kernel merges its split rows (each launch marks afresh)
-    ap.merge_flag = reinterpret_cast<uint32_t *>(at(ws, L.merge_flag));
-    ap.epoch = next_merge_epoch();
+    // The statistics' split count, and who merges the split rows, depend on
+    // the launch's layer count (each launch that marks marks afresh).
+    const int32_t lse_ns = attn_span_splits(ap, attn_pairs_per_block(false), lt.n);
+    const bool merge_lse = colsum_merges_lse(lse_ns, (int64_t)n_q * ap.group, img->n_vis, kv->n_kv_heads, lt.n);
+    ap.merge_flag = merge_lse ? nullptr : reinterpret_cast<uint32_t *>(at(ws, L.merge_flag));
+    if (!merge_lse) ap.epoch = next_merge_epoch();
     cs.clear_u32 = ap.merge_flag;
-    cs.clear_n = (int32_t)(L.plan.max_items * lt.n);
+    cs.clear_n = merge_lse ? 0 : (int32_t)(L.plan.max_items * lt.n);
+    cs.lse_part_m = merge_lse ? ap.part_m : nullptr;
+    cs.lse_part_l = merge_lse ? ap.part_l : nullptr;
+    cs.lse_ns = merge_lse ? lse_ns : 0;
+    cs.lse_ppb = merge_lse ? attn_pairs_per_block(false) : 0;
+    cs.lse_layer_stride = merge_lse ? (int64_t)L.plan.max_items * attn_pairs_per_block(false) : 0;
     hipError_t e = launch_attn(ap, D, false, stream, &lt);
     if (e != hipSuccess) return hip_fail(e, "row statistics");
     fp.accumulate = (l0 > 0 || accumulate) ? 1 : 0;

@@ -310,7 +310,7 @@ struct AttnParams {
   // that finds every split of its block marked merges the block into
   // row_b / lse_out.  Marks of another epoch count as unset; the column sums
   // that follow clear them, so that a captured launch, which replays one
-  // epoch, starts without marks too.
+  // epoch, starts without marks too.  (Null: the column sums merge.)
   uint32_t *merge_flag;
   uint32_t epoch;
 };
@@ -433,6 +433,13 @@ struct ColsumParams {
   const float2 *f32_ml;
   int32_t lse_ns;
   float *lse_out;           // natural log
+  // bf16, launches of 8-wave workgroups: row log-sum-exps merged by every
+  // workgroup from the statistics' split partials (lse_ns <= kLseRegSplits
+  // splits of lse_ppb-pair blocks) instead of read from row_b; nullable.
+  const float *lse_part_m;
+  const float *lse_part_l;
+  int32_t lse_ppb;
+  int64_t lse_layer_stride;  // partials per layer of a multi-layer launch
   uint32_t *clear_u32;      // nullable: [clear_n] words cleared by the kernel (bf16)
   int32_t clear_n;
   // nullable: arrival counters, one per key block, cleared beforehand; the
@@ -651,5 +658,16 @@ constexpr int64_t attn_max_items(int64_t n_pb, int64_t n_kv_heads, bool with_val
 constexpr int kAttnKeyTile = 64;         // keys per LDS tile
 constexpr int64_t kMaxStrideBytes = int64_t(1) << 25;  // row strides below 32 MiB: a key tile spans < 2 GiB
 constexpr int kColsumKeysPerBlock = 256;  // visual keys per finalized block
+// Launches below this many column-sum workgroups take 8-wave ones.
+constexpr int64_t kColsumFourWaveBlocks = 512;
+constexpr int64_t colsum_blocks(int32_t n_vis, int32_t n_kv_heads, int32_t n_layers) {
+  return int64_t((n_vis + kColsumKeysPerBlock - 1) / kColsumKeysPerBlock) * n_kv_heads * n_layers;
+}
+// Split statistics rows are merged by the column-sum workgroups when these
+// are the 8-wave ones (at most two rounds, so few repeat the merge) and a KV
+// head has at most this many splits and rows; otherwise the statistics kernel
+// merges them once, at its end.
+constexpr int kLseRegSplits = 24;
+constexpr int kColsumMaxLsePairs = 4096;
 
 }  // namespace conduit

@@ -131,10 +131,13 @@ __device__ __forceinline__ void lds_dma16(__amdgpu_buffer_rsrc_t r, uint32_t lds
 constexpr int kQTile = 64;
 constexpr int kQStages = 4;
 constexpr int kBTiles = 8;
-template <int D>
+constexpr int kMergeRows = 2;    // rows per thread that are merged at once
+constexpr int kMergeLoads = 6;   // splits asked for together
+template <int D, bool MERGE>
 struct ColsumSmem {
   alignas(16) u16 q[kQStages][kQTile][D + 8];
-  alignas(16) float nb[kBTiles][kQTile];  // -b of the tiles' rows (doubled for RMS; past the last row: -inf)
+  // MERGE: every row's (and two tiles that are read ahead), else a ring
+  alignas(16) float nb[MERGE ? kColsumMaxLsePairs / kQTile + 2 : kBTiles][kQTile];  // -b of the tiles' rows (doubled for RMS; past the last row: -inf)
   uint32_t off[kBTiles][kQTile];          // byte offsets of the tiles' rows
   int64_t row[kColsumKeysPerBlock];       // cache row of each key of the workgroup
   float part[kColsumKeysPerBlock];        // RH = 2: column sums of the odd row halves
@@ -160,7 +163,13 @@ struct ColsumSmem {
 // product alone 32): 66 cycles per product over the whole kernel at 65,536
 // keys x 1,792 rows x 4 layers (0.94 M; 1.40 M with 32 keys per wave, operands
 // read one product ahead and one 8-wave workgroup per CU).
-template <int D, int RH>
+// MERGE (RH = 2 only): the rows' b are merged from the statistics' split
+// partials by every workgroup, asked for at its start and reduced after the K
+// rows have been asked for, in place of the statistics kernel's merge, whose
+// chain of waits at its end costs about 4 us (16k scoring 0.985 of the 32-key
+// kernels' speed with that merge, 1.018 with this one; a single-image step
+// 71.6 and 69.6 us).
+template <int D, int RH, bool MERGE>
 __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumParams p, LayerTable lt, int rms) {
   constexpr int KS = D / 16;
   constexpr int kThreads = 256 * RH, W = kThreads / 64;
@@ -174,6 +183,9 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
                "s"(p.k_stride), "s"(p.v_stride), "s"(p.pages.table), "s"(p.pages.shift), "s"(p.pages.n_pages),
                "s"(p.n_kv_heads), "s"(p.group), "s"(p.n_q_heads), "s"(p.n_q), "s"(p.n_vis), "s"(p.scale_log2),
                "s"(p.clear_u32), "s"(p.clear_n), "s"(p.done), "s"(p.tbl.n_images), "s"(lt.n));
+  if constexpr (MERGE)
+    asm volatile("" ::"s"(p.lse_part_m), "s"(p.lse_part_l), "s"(p.lse_ns), "s"(p.lse_ppb), "s"(p.lse_layer_stride),
+                 "s"(p.lse_out));
   // This layer's pointers, in locals: p itself stays unwritten (a written
   // kernel parameter holding the image table would be copied to scratch).
   const bool ml = lt.n > 0;
@@ -186,7 +198,7 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
   const float *vnorm_in = ml ? layer_entry(lt.vnorm, layer) : p.vnorm_in;
   float *colsum_part = p.colsum_part + part_off;
   float *vsq_part = p.vsq_part + part_off;
-  __shared__ ColsumSmem<D> sm;
+  __shared__ ColsumSmem<D, MERGE> sm;
   float *const nb = &sm.nb[0][0];
 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -287,13 +299,57 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
   };
   // Offsets of tiles 0..5 and -b of tiles 0..3.  (Threads of the upper half
   // hold the same rows as the lower half's: they take the odd pairs.)
-  // The loads of b stay in flight until the K rows have been asked for.
+  // The loads of b (MERGE: of the first rows' split partials) stay in flight
+  // until the K rows have been asked for.
   float b_first = 0.f;
+  // MERGE: b = M + log2(sum_s l_s 2^(m_s - M)) over the splits of a row, in
+  // split order, kMergeRows rows r0 + tid + i kThreads per thread; the first
+  // key block also writes lse_out.  Slot (pb n_kv_heads + kvh) ns + s holds
+  // split s of the rows of block pb.
+  float mv[kMergeRows][MERGE ? kLseRegSplits : 1], lv[kMergeRows][MERGE ? kLseRegSplits : 1];
+  auto ask_rows = [&](int r0) __attribute__((always_inline)) {
+    const float *pm = p.lse_part_m + layer * p.lse_layer_stride, *pl = p.lse_part_l + layer * p.lse_layer_stride;
+#pragma unroll
+    for (int i = 0; i < kMergeRows; ++i) {
+      const int r = min(r0 + tid + i * kThreads, n_pair - 1);
+      const int pb = r / p.lse_ppb;
+      const int64_t at = ((int64_t)pb * p.n_kv_heads + kvh) * p.lse_ns * p.lse_ppb + (r - pb * p.lse_ppb);
+#pragma unroll
+      for (int s0 = 0; s0 < kLseRegSplits; s0 += kMergeLoads) {
+#pragma unroll
+        for (int u = 0; u < kMergeLoads; ++u) mv[i][s0 + u] = -kInf, lv[i][s0 + u] = 0.f;
+        if (s0 < p.lse_ns) {
+#pragma unroll
+          for (int u = 0; u < kMergeLoads; ++u) {
+            const int64_t e = at + (int64_t)min(s0 + u, p.lse_ns - 1) * p.lse_ppb;
+            mv[i][s0 + u] = pm[e];
+            lv[i][s0 + u] = pl[e];
+          }
+        }
+      }
+    }
+  };
+  auto merge_rows = [&](int r0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < kMergeRows; ++i) {
+      const int r = r0 + tid + i * kThreads;
+      float M = mv[i][0], L = 0.f;
+#pragma unroll
+      for (int u = 1; u < kLseRegSplits; ++u) M = fmaxf(M, mv[i][u]);  // (clamped loads repeat the last split)
+#pragma unroll
+      for (int u = 0; u < kLseRegSplits; ++u) L += u < p.lse_ns ? fast_exp2(mv[i][u] - M) * lv[i][u] : 0.f;
+      const float b = M + __log2f(L);
+      if (r < n_tiles * kQTile) nb[r] = neg_b(b, r);
+      if (p.lse_out && !ml && blockIdx.x == 0 && r < n_pair)
+        p.lse_out[(int64_t)(r / G) * p.n_q_heads + kvh * G + r % G] = b * kLn2;
+    }
+  };
+  if constexpr (MERGE) ask_rows(0);
   {
     if (wave == 2 || wave == 3) next_rows();
     if (wave < 4) {
       sm.off[0][tid] = row_off();
-      b_first = load_b();
+      if constexpr (!MERGE) b_first = load_b();
     }
     if (wave < 2) {  // to the rows of tiles 4 and 5
       next_rows();
@@ -352,7 +408,15 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
       for (int ks = 0; ks < KS; ++ks) kreg[cb][ks] = as_bf16x8(ld16(krow + ks * 16));
     }
   }
-  if (wave < 4) nb[tid] = neg_b(b_first, tid);
+  if constexpr (MERGE) {
+    merge_rows(0);
+    for (int r0 = kMergeRows * kThreads; r0 < n_pair; r0 += kMergeRows * kThreads) {
+      ask_rows(r0);
+      merge_rows(r0);
+    }
+  } else {
+    if (wave < 4) nb[tid] = neg_b(b_first, tid);
+  }
   __builtin_amdgcn_s_waitcnt(0);  // this wave's Q transfers (invisible to the compiler)
   __syncthreads();
 
@@ -381,7 +445,7 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
   // -b of the rows of sub-tile `sub` of a tile that this lane holds: register
   // v of lane (col, half) is row 8*(v/4) + 4*half + v%4 of its sub-tile
   auto b_of = [&](int tile, int sub) __attribute__((always_inline)) {
-    return nb + (tile & (kBTiles - 1)) * kQTile + 32 * sub + 4 * half;
+    return nb + (MERGE ? tile : tile & (kBTiles - 1)) * kQTile + 32 * sub + 4 * half;
   };
   f32x4 nb4 = *reinterpret_cast<const f32x4 *>(b_of(0, wsub));  // rows 0..3 of the current sub-tile
   // One sub-step: cur = S(i), with b at bp; nxt receives S(i+1) from the
@@ -456,7 +520,7 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
     // -b of the rows of tiles t+4, t+5 and the offsets of t+6, t+7
     float bv = 0.f;
     if (wave < 2) {
-      bv = load_b();
+      if constexpr (!MERGE) bv = load_b();
       next_rows();
       sm.off[(t + 6) & kMod][tid] = row_off();
     }
@@ -475,7 +539,7 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
         step(sb, sa, s3, wsub, b_of(t + 1, wsub), b_of(t + 2, wsub),
              [&](int j) __attribute__((always_inline)) { slot(kStep + j); });
     }
-    if (wave < 2) sm.nb[(t + 4) & kMod][tid] = neg_b(bv, (t + 4) * kQTile + tid);
+    if (!MERGE && wave < 2) sm.nb[(t + 4) & kMod][tid] = neg_b(bv, (t + 4) * kQTile + tid);
     __builtin_amdgcn_s_waitcnt(0);  // this wave's transfers have landed
     __syncthreads();
   }
@@ -667,15 +731,18 @@ hipError_t launch_colsum(const ColsumParams &p, int head_dim, bool bf16, bool rm
     // Two 4-wave workgroups per CU when the launch has that many, else 8-wave
     // ones (4-layer document: 688 us with 8 waves, 573 with 4; one 16k layer,
     // one workgroup per CU: 25 us with 8 waves, a wave per SIMD idles with 4).
-    const bool two = (int64_t)grid.x * grid.y * grid.z >= 512;
+    const bool two = colsum_blocks(p.n_vis, p.n_kv_heads, lt0.n > 0 ? lt0.n : 1) >= kColsumFourWaveBlocks;
+    if (p.lse_part_m && (two || p.lse_ns > kLseRegSplits || (int64_t)p.n_q * p.group > kColsumMaxLsePairs))
+      return hipErrorInvalidValue;
     ProfScope ps("colsum", s);
-    if (head_dim == 128) {
-      if (two) colsum_bf16_kernel<128, 1><<<grid, 256, 0, s>>>(p, lt0, rms);
-      else colsum_bf16_kernel<128, 2><<<grid, 512, 0, s>>>(p, lt0, rms);
-    } else {
-      if (two) colsum_bf16_kernel<64, 1><<<grid, 256, 0, s>>>(p, lt0, rms);
-      else colsum_bf16_kernel<64, 2><<<grid, 512, 0, s>>>(p, lt0, rms);
-    }
+    auto launch = [&](auto d) {
+      constexpr int D = decltype(d)::value;
+      if (two) colsum_bf16_kernel<D, 1, false><<<grid, 256, 0, s>>>(p, lt0, rms);
+      else if (p.lse_part_m) colsum_bf16_kernel<D, 2, true><<<grid, 512, 0, s>>>(p, lt0, rms);
+      else colsum_bf16_kernel<D, 2, false><<<grid, 512, 0, s>>>(p, lt0, rms);
+    };
+    if (head_dim == 128) launch(std::integral_constant<int, 128>{});
+    else launch(std::integral_constant<int, 64>{});
   } else {
     dim3 grid((p.n_vis + 63) / 64, p.n_kv_heads);
     ProfScope ps("colsum_f32", s);

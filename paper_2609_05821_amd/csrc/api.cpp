@@ -713,7 +713,10 @@ struct ResidualLayout {
   int32_t n_splits, tiles_per_split, pairs_pad;
 };
 
-ResidualLayout residual_layout(const conduit_kv *kv, int32_t n_q, int32_t n_vis, int32_t n_samples, bool iso) {
+// by_rounds: key splits counted by rounds of workgroups; otherwise by a target
+// number of workgroups, the count whose workspace every caller has.
+ResidualLayout residual_layout(const conduit_kv *kv, int32_t n_q, int32_t n_vis, int32_t n_samples, bool iso,
+                               bool by_rounds) {
   ResidualLayout L{};
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes, 256); return at; };
@@ -724,10 +727,27 @@ ResidualLayout residual_layout(const conduit_kv *kv, int32_t n_q, int32_t n_vis,
     const int64_t n_pb = (pairs + kResidualPairs - 1) / kResidualPairs;
     const int tiles = (n_vis + kAttnKeyTile - 1) / kAttnKeyTile;
     const int64_t base = n_pb * kv->n_kv_heads * n_samples;
-    int splits = (int)std::min<int64_t>((kResidualTargetBlocks + base - 1) / base,
-                                        std::max(1, tiles / kResidualMinTiles));
-    splits = std::max(splits, (tiles + kResidualMaxTiles - 1) / kResidualMaxTiles);
-    splits = std::max(1, splits);
+    const int lo = std::max(1, (tiles + kResidualMaxTiles - 1) / kResidualMaxTiles);
+    int splits = std::max(lo, (int)std::min<int64_t>((kResidualTargetBlocks + base - 1) / base,
+                                                     std::max(1, tiles / kResidualMinTiles)));
+    if (by_rounds) {
+      // The count with the least estimated time: rounds of one workgroup per
+      // CU times the tiles of a split and kResidualItemTiles more (a
+      // workgroup's start and its partial sums), the smaller count on ties.
+      // 16,384 visual tokens x 896 pairs x 4 heads x 5 samples: 9 splits (720
+      // workgroups, 3 rounds of 29 tiles) 209 us, 8 (640, 3 rounds of 32)
+      // 216-222 us.
+      int64_t best = INT64_MAX;
+      for (int ns = lo; ns <= std::max(lo, tiles / kResidualMinTiles); ++ns) {
+        const int64_t rounds = (base * ns + kResidualWorkgroups - 1) / kResidualWorkgroups;
+        const int64_t cost = rounds * ((tiles + ns - 1) / ns + kResidualItemTiles);
+        if (cost < best) {
+          best = cost;
+          splits = ns;
+        }
+        if (base * ns >= 4 * kResidualWorkgroups) break;  // finer splits only write more partials
+      }
+    }
     L.tiles_per_split = (tiles + splits - 1) / splits;
     L.n_splits = (tiles + L.tiles_per_split - 1) / L.tiles_per_split;
     L.pairs_pad = (int32_t)(n_pb * kResidualPairs);
@@ -744,7 +764,8 @@ size_t conduit_residual_workspace_bytes(const conduit_kv *kv, int32_t n_q, const
   if (!kv || !img || n_q < 1 || n_samples < 1 || kv->n_kv_heads < 1 || kv->n_q_heads < kv->n_kv_heads ||
       img->n_vis < 1 || (kv->head_dim != 64 && kv->head_dim != 128))
     return 0;
-  return residual_layout(kv, n_q, img->n_vis, n_samples, iso != 0).total;
+  return std::max(residual_layout(kv, n_q, img->n_vis, n_samples, iso != 0, true).total,
+                  residual_layout(kv, n_q, img->n_vis, n_samples, iso != 0, false).total);
 }
 
 conduit_status conduit_residual_error(const conduit_kv *kv, const void *q, int32_t n_q, int32_t q_pos0,
@@ -779,7 +800,9 @@ conduit_status conduit_residual_error(const conduit_kv *kv, const void *q, int32
   ImageTable tbl;
   st = check_images(img, q_pos0, &tbl);
   if (st) return st;
-  const ResidualLayout L = residual_layout(kv, n_q, img->n_vis, n_samples, iso);
+  // (a workspace that holds only the target count's partials takes that count)
+  ResidualLayout L = residual_layout(kv, n_q, img->n_vis, n_samples, iso, true);
+  if (ws_bytes < L.total) L = residual_layout(kv, n_q, img->n_vis, n_samples, iso, false);
   st = check_ws(ws, ws_bytes, L.total);
   if (st) return st;
   char *w = static_cast<char *>(ws);

@@ -625,6 +625,8 @@ hipError_t static_score_scratch(void **out);
 constexpr int kResidualPairs = 256;
 constexpr int kResidualMinTiles = 8;
 constexpr int kResidualTargetBlocks = 512;
+constexpr int kResidualWorkgroups = 256;  // resident at once
+constexpr int kResidualItemTiles = 10;
 constexpr int kResidualMaxTiles = 32;   // key metadata of a split is held in LDS
 
 // Tiling shared by the host layer (workspace sizing) and the kernels.

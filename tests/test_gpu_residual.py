@@ -149,3 +149,29 @@ def test_residual_tile_pipeline(n_vis, d):
             O.projected_displacements(L["v"], w.img_pos, w.img_off)
         ref = O.residual_error(L["q"], L["k"], w.q_pos0, w.img_pos, w.img_off, mask, xi)
         assert_scores(to_f64(got), ref, rtol=rtol(w), what="err")
+
+
+def test_residual_smallest_workspace(monkeypatch):
+    """Split counts depend on the workspace given (the full size, and less): the errors agree, and a workspace below
+    the least one is refused.  A split rounds its weights the same way whatever the count, so the entries differ by
+    fp32 sums only; the bound is half the one against the oracle."""
+    w = W.custom(1, 28, 4, 128, 32, 3, [1024] * 8, 2, "bf16", n_relevant=1, seed=31)
+    L = w.layer(0, fresh=False)
+    k, v, q = (to_dev(L[x]) for x in ("k", "v", "q"))
+    kv = api.kv_desc(k, v, w.n_q_heads)
+    img = api.ImageTable(w.img_pos, w.img_off)
+    lse = row_lse(w, kv, q, img, O.NORM_CAUSAL_ROW)
+    refreshed = to_dev((np.arange(w.n_vis) % 7 == 0).astype(np.uint8))
+    z = to_dev(W.iso_directions(w, 0, M))
+    full = run(w, kv, q, img, lse, refreshed, z)
+    need = api.residual_workspace_bytes(kv, w.n_q, img, M, True)
+    monkeypatch.setattr(api, "_workspace", lambda nbytes, device, ws: ws)
+    for part in (1.0, 0.95, 0.9, 0.5):
+        err = torch.full_like(full, -1.0)
+        ws = torch.empty(int(need * part), dtype=torch.uint8, device=DEV)
+        try:
+            api.conduit_residual_error(kv, q, w.q_pos0, img, lse, refreshed, err, z=z, ws=ws)
+        except api.ConduitError:
+            assert part < 1.0 and bool((err == -1.0).all())
+            continue
+        assert float((err / full - 1).abs().max()) < 1e-2

@@ -197,7 +197,8 @@ def test_visual_only_statistics_far_below_a_text_key(boost):
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("n_q,hkv,g,images", [(1, 1, 1, [1]), (9, 2, 7, [255]), (64, 1, 1, [256]), (13, 2, 5, [200, 57]),
-                                              (32, 1, 4, [511, 2]), (43, 4, 3, [1000] * 3), (65, 2, 7, [2049]), (200, 2, 7, [2049]),
+                                              (32, 1, 4, [511, 2]), (43, 4, 3, [1000] * 3), (65, 2, 7, [2049]),
+                                              (200, 2, 7, [2049]),
                                               (7, 8, 7, [16384]), (43, 8, 3, [9000, 7500]), (90, 8, 7, [20000])])
 def test_score_tile_pipeline(d, n_q, hkv, g, images):
     """Row counts around whole 64-row tiles (one tile, odd, even, ragged), key counts around whole 256-key

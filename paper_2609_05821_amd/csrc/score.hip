@@ -371,10 +371,12 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
   __syncthreads();
   // tiles 0 and 1, and 2 (RH = 1: the first iteration takes 3) or 2 and 3
   each([&](auto n) __attribute__((always_inline)) { dma_q(n, sm.off[0], sm.off[1], q_lds, q_lds + kStageB); });
-  each([&](auto n) __attribute__((always_inline)) {
-    if (RH == 2 || (decltype(n)::value < 2 * kFull ? decltype(n)::value % 2 == 0 : !left_b))
-      dma_q(n, sm.off[2], sm.off[3], q_lds + 2 * kStageB, q_lds + 3 * kStageB);
-  });
+  // (a span of one or two tiles uses nothing of what it reads from them)
+  if (n_tiles > 2)
+    each([&](auto n) __attribute__((always_inline)) {
+      if (RH == 2 || (decltype(n)::value < 2 * kFull ? decltype(n)::value % 2 == 0 : !left_b))
+        dma_q(n, sm.off[2], sm.off[3], q_lds + 2 * kStageB, q_lds + 3 * kStageB);
+    });
 
   // This lane's key columns, held as the B operands for every row tile.
   bf16x8 kreg[2][KS];

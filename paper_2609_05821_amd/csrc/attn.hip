@@ -718,9 +718,12 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
     // sub-tile beyond the previous trigger, so an item restarts at most once
     // per iteration.  Without a running-maximum rescale the sub-steps have no
     // branch on the probabilities, and O^T is written by matrix products
-    // only.  Statistics only keep an online maximum (their rescale is one
-    // multiply; with the visual-only domain the first keys of a split are
-    // often outside it, which a fixed reference would turn into restarts).
+    // only.  Statistics take the fixed reference in an item's first attempt
+    // alone; their second one keeps an online maximum (its rescale is one
+    // multiply), which suits any logits, and neither sets nor reads the
+    // restart flag: an item takes at most two attempts.  With the visual-only
+    // domain the first keys of a split are often outside it, which a fixed
+    // reference would turn into restarts: the only attempt is the online one.
     constexpr float kHeadroom = 32.f;
     constexpr float kHeadroomSum = 4294967296.f;  // 2^kHeadroom
     float m_seen = kMInit;  // (with values)
@@ -728,9 +731,7 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
     for (int attempt = 0;; ++attempt) {
 #pragma unroll
     for (int cb = 0; cb < NC; ++cb) l[cb] = 0.f;
-    // Statistics over every key of the causal range take a fixed reference
-    // in their first attempt like the values path; after a restart, or with
-    // the visual-only domain, they keep the online maximum.
+    over = false;
     const bool fixed_ref = PV ? attempt == 0 : attempt == 0 && !p.vis_only;
     if constexpr (!PV) m[0] = m[NC - 1] = kMInit;
     if constexpr (PV) {
@@ -757,7 +758,6 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
         m[cb] = fmaxf(PV ? fmaxf(sub_max(sa[cb]), m_seen) : sub_max(sa[cb]), kMInit);
       }
       if constexpr (PV) m_seen = m[0];
-      over = false;
     }
     const int gen = ++attempt_id;  // the workgroup's attempts in order (uniform, never repeats)
     bool restart = false;
@@ -1045,10 +1045,10 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
         if (t0 + KT < kend)
           st_step(m1, sb, sa, k3, (ti + 1) & 7, t0 + KT,  // P(t+1) | S(t+2)
                   [&](int j) __attribute__((always_inline)) { slot(NC * KS + j); });
-        if (__ballot(over) != 0 && lane == 0) s_restart = gen;
+        if (fixed_ref && __ballot(over) != 0 && lane == 0) s_restart = gen;
         vm_wait<0>();
         __syncthreads();
-        restart = __builtin_amdgcn_readfirstlane(s_restart) == gen;
+        restart = fixed_ref && __builtin_amdgcn_readfirstlane(s_restart) == gen;
         if (!more2 || restart) break;
         t0 += 2 * KT;
         ks = k2;

@@ -232,3 +232,80 @@ def test_score_tile_pipeline(d, n_q, hkv, g, images):
         assert float((a.double() / ref[r] - 1).abs().max()) < 2e-4
         assert float((s.double() / (ref[r] * vnorm) - 1).abs().max()) < 2e-4
         assert torch.equal(a, a_out)
+
+
+def _jump_layer(gen, d, n_q, hkv, g, n_ctx):
+    """Keys and queries ~ N(0, 1) with every fourth 64-key tile holding one key, in its first or its second half,
+    that most rows score 30 to 50 nats above the rest, more from tile to tile."""
+    b = torch.nn.functional.normalize(torch.randn(hkv, d, generator=gen, device=DEV), dim=1)
+    k = torch.randn(n_ctx, hkv, d, generator=gen, device=DEV)
+    jump = torch.arange(3 * 64, n_ctx - n_q, 4 * 64, device=DEV)
+    jump += torch.where(torch.arange(len(jump), device=DEV) % 2 == 0, 40, 5)
+    amp = torch.linspace(30.0, 50.0, len(jump), device=DEV)
+    k[jump] = 0.5 * d ** 0.5 * amp[:, None, None] * b
+    q = torch.randn(n_q, hkv * g, d, generator=gen, device=DEV) + 2.0 * b.repeat_interleave(g, 0)
+    v = torch.randn(n_ctx, hkv, d, generator=gen, device=DEV)
+    return tuple(x.to(torch.bfloat16) for x in (k, v, q))
+
+
+def _score64(k, v, q, q_pos0, vis):
+    """Causal-row a_t, a_t ||V_t|| and the row log-sum-exps of one layer in float64; and the rows' largest logit less
+    that of their first 64 keys."""
+    (n_q, hq, d), hkv = q.shape, k.shape[1]
+    hidden = torch.arange(len(k), device=DEV)[None] > q_pos0 + torch.arange(n_q, device=DEV)[:, None]
+    a = torch.zeros(len(vis), dtype=torch.float64, device=DEV)
+    lse, gap = (torch.zeros(n_q, hq, dtype=torch.float64, device=DEV) for _ in range(2))
+    for h in range(hq):
+        z = (q[:, h].double() @ k[:, h // (hq // hkv)].double().t() / d ** 0.5).masked_fill(hidden, -torch.inf)
+        lse[:, h] = torch.logsumexp(z, dim=1)
+        gap[:, h] = z.amax(1) - z[:, :64].amax(1)
+        a += torch.softmax(z, dim=1)[:, vis].sum(0) / (n_q * hq)
+    return a, a * v[vis].double().flatten(1).norm(dim=1), lse, gap
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_q,hkv,g,n_vis,layers", [(12, 1, 4, 300, 1), (33, 2, 7, 2500, 1), (20, 8, 2, 16500, 1),
+                                                    (33, 2, 7, 2500, 3), (40, 4, 3, 4200, 9)])
+def test_score_late_keys_far_above_the_first(d, n_q, hkv, g, n_vis, layers):
+    """Keys in later tiles of every split of the statistics out-score the split's first ones by more than the 32 log2
+    units that a fixed reference maximum bears: those items are done again with an online maximum, once.  One split,
+    several, more than the column sums merge; below and above 512 column-sum workgroups; one layer and several.
+    Logits stay below 210 log2 units, so that the fp32 exponent and the fp32 sums of d exact products err by less
+    than 5e-5: 1e-4 relative is asked for."""
+    gen = torch.Generator(device=DEV).manual_seed(n_vis + d + layers)
+    q_pos0, n_ctx = 7 + n_vis, 7 + n_vis + n_q
+    L = [_jump_layer(gen, d, n_q, hkv, g, n_ctx) for _ in range(layers)]
+    vis = torch.arange(5, 5 + n_vis, device=DEV)
+    img = api.ImageTable(np.array([5], np.int32), np.array([0, n_vis], np.int32))
+    ref = [_score64(k, v, q, q_pos0, vis) for k, v, q in L]
+    assert float((ref[0][3] > 23.0).double().mean()) > 0.25
+    kvs, qs = [api.kv_desc(k, v, hkv * g) for k, v, _ in L], [q for _, _, q in L]
+    s, a = (torch.full((n_vis,), 7.0, device=DEV) for _ in range(2))
+    if layers > 1:
+        api.conduit_score_layers(kvs, qs, q_pos0, img, s, a)
+    else:
+        lse = torch.zeros(n_q, hkv * g, device=DEV)
+        api.conduit_score(kvs[0], qs[0], q_pos0, img, s, a, row_lse_out=lse)
+        assert float((lse.double() / ref[0][2] - 1).abs().max()) < 1e-4
+    assert float((a.double() / sum(r[0] for r in ref) - 1).abs().max()) < 1e-4
+    assert float((s.double() / sum(r[1] for r in ref) - 1).abs().max()) < 1e-4
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_q,hkv,g,n_vis", [(33, 2, 7, 2500), (20, 8, 2, 16500)])
+def test_score_with_a_nan_query_row(d, n_q, hkv, g, n_vis):
+    """A NaN in one row's query: the call returns, that row's log-sum-exp is NaN and the other rows' are theirs."""
+    gen = torch.Generator(device=DEV).manual_seed(n_vis + d)
+    q_pos0, n_ctx = 7 + n_vis, 7 + n_vis + n_q
+    k, v, q = _jump_layer(gen, d, n_q, hkv, g, n_ctx)
+    vis = torch.arange(5, 5 + n_vis, device=DEV)
+    ref = _score64(k, v, q, q_pos0, vis)[2]
+    q[n_q // 2, 1, 3] = torch.nan
+    s, a = (torch.zeros(n_vis, device=DEV) for _ in range(2))
+    lse = torch.zeros(n_q, hkv * g, device=DEV)
+    api.conduit_score(api.kv_desc(k, v, hkv * g), q, q_pos0,
+                      api.ImageTable(np.array([5], np.int32), np.array([0, n_vis], np.int32)), s, a, row_lse_out=lse)
+    bad = torch.zeros(n_q, hkv * g, dtype=torch.bool, device=DEV)
+    bad[n_q // 2, 1] = True
+    assert torch.equal(torch.isnan(lse), bad)
+    assert float((lse.double() / ref - 1)[~bad].abs().max()) < 1e-4

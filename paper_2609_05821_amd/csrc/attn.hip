@@ -344,7 +344,10 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
   constexpr int KS = D / 16;      // MFMA k-steps over the head dimension
   constexpr int DT = D / 32;      // 32-row tiles of O^T
   __shared__ AttnSmem<D, PV> sm;
-  __shared__ int s_restart;  // attempt id of the item being restarted (see kHeadroom)
+  // attempt id of the item being restarted (see kHeadroom), one word for the
+  // even and one for the odd pairs of tiles: a word is written again only
+  // after another barrier has followed its reads
+  __shared__ int s_restart[2];
   __shared__ int s_last;     // statistics: this workgroup holds the last split of its block
 
   // The parameter block is read in one go (otherwise each scalar is loaded
@@ -423,7 +426,7 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
   const int n_items = n_plan_items * n_layers;
 
   const int grid = gridDim.x, g = blockIdx.x;
-  if (tid == 0) s_restart = 0;
+  if (tid < 2) s_restart[tid] = 0;
   int attempt_id = 0;
   if constexpr (!PV) {
     if (p.vis_only) {
@@ -922,10 +925,11 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
                     if (j % kPlanStep == 0 && j / kPlanStep < kPlanParts) plan_part(j / kPlanStep, t0 + 2 * KT);
                   });
         }
-        if (__ballot(over) != 0 && lane == 0) s_restart = gen;
+        const int word = (t0 / (2 * KT)) & 1;
+        if (__ballot(over) != 0 && lane == 0) s_restart[word] = gen;
         vm_wait<0>();
         __syncthreads();
-        restart = __builtin_amdgcn_readfirstlane(s_restart) == gen;
+        restart = __builtin_amdgcn_readfirstlane(s_restart[word]) == gen;
         if (!more2 || restart) break;
         t0 += 2 * KT;
         ks = k2;
@@ -1045,10 +1049,11 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
         if (t0 + KT < kend)
           st_step(m1, sb, sa, k3, (ti + 1) & 7, t0 + KT,  // P(t+1) | S(t+2)
                   [&](int j) __attribute__((always_inline)) { slot(NC * KS + j); });
-        if (fixed_ref && __ballot(over) != 0 && lane == 0) s_restart = gen;
+        const int word = (t0 / (2 * KT)) & 1;
+        if (fixed_ref && __ballot(over) != 0 && lane == 0) s_restart[word] = gen;
         vm_wait<0>();
         __syncthreads();
-        restart = fixed_ref && __builtin_amdgcn_readfirstlane(s_restart) == gen;
+        restart = fixed_ref && __builtin_amdgcn_readfirstlane(s_restart[word]) == gen;
         if (!more2 || restart) break;
         t0 += 2 * KT;
         ks = k2;

@@ -729,6 +729,7 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
     // reference would turn into restarts: the only attempt is the online one.
     constexpr float kHeadroom = 32.f;
     constexpr float kHeadroomSum = 4294967296.f;  // 2^kHeadroom
+    constexpr int kNoTile = PV ? 4 : 0;
     float m_seen = kMInit;  // (with values)
     bool over = false;
     for (int attempt = 0;; ++attempt) {
@@ -743,6 +744,11 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
     }
     if (attempt > 0) first_tiles();
     if constexpr (PV) {
+      // The first sub-step's O^T products have no probabilities yet (zeros):
+      // their V operands are zeros too, for a value may be infinite.  Stage
+      // kNoTile is filled in the second iteration.
+      for (int i = tid; i < 32 * Geo::vPitch / 8; i += kThreads)
+        st16(&sm.v[kNoTile][32][0] + 8 * i, u32x4{0, 0, 0, 0});
       vm_wait<2 * kFull + 2 * vFull>();  // K(0)
     } else {
 #pragma unroll
@@ -870,7 +876,7 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
         pk[0] = as_bf16x8(pn[0]);
         pk[1] = as_bf16x8(pn[1]);
       };
-      int vlast = 0;
+      int vlast = kNoTile;
       int t0 = kbeg, ks = 0, vs = 0;  // stages of tile t
       Group gr;
       // The next iteration's transfers: K(t+3), K(t+4), V(t+2), V(t+3), in

@@ -267,3 +267,24 @@ def test_refresh_tile_pipeline(d, n_ctx, n_rows, hkv, g):
     err = (out.double() - ref).norm(dim=2) / ref.norm(dim=2)
     assert float(err.max()) < 1e-2
     assert float((lse.double() - ref_lse).abs().max()) < 1e-4
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_ctx,n_rows", [(200, 30), (3000, 300)])
+def test_refresh_infinite_value(d, n_ctx, n_rows):
+    """An infinite value in the second half of the first key tile, seen by every row: infinite outputs in its head and
+    dim, with its sign, and everything else as without it (no probability of zero is multiplied by it)."""
+    hkv, g, key, head, dim = 2, 7, 40, 1, 5
+    gen = torch.Generator(device=DEV).manual_seed(n_ctx + d)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device=DEV).to(torch.bfloat16)
+    k, v, q = rnd(n_ctx, hkv, d), rnd(n_ctx, hkv, d), rnd(n_rows, hkv * g, d)
+    pos = (64 + torch.sort(torch.randperm(n_ctx - 64, generator=gen, device=DEV)[:n_rows]).values).to(torch.int32)
+    outs = []
+    for x in (float(v[key, head, dim]), -torch.inf):
+        v[key, head, dim] = x
+        out = torch.empty_like(q)
+        api.conduit_refresh_attn(api.kv_desc(k, v, hkv * g), q, pos, out)
+        outs.append(out)
+    want = outs[0].clone()
+    want[:, head * g:(head + 1) * g, dim] = -torch.inf
+    assert torch.equal(outs[1], want)

@@ -166,6 +166,10 @@ __global__ __launch_bounds__(kThreads, 1) void residual_bf16_kernel(ResidualPara
   for (int dt = 0; dt < DT; ++dt) y[dt] = f32x16{};
 
   if (n_t > 0) {
+    // The first sub-step's y^T products have no probabilities yet (zeros):
+    // their displacement operands (stage 3, X(-1)) are zeros too, for a
+    // displacement may be infinite.
+    for (int i = tid; i < 32 * Sm::xPitch / 8; i += kThreads) st16(&sm.x[3][32][0] + 8 * i, u32x4{0, 0, 0, 0});
     // K(0), X(0); K(1), X(1); K(2)
     uint32_t rows[kGroup];
 #pragma unroll
@@ -266,7 +270,7 @@ __global__ __launch_bounds__(kThreads, 1) void residual_bf16_kernel(ResidualPara
           rows[n] = row_of(n, t + 4, t + 3);  // the next iteration's
         }
       };
-      step(sa, sb, k1, 0, t > 0 ? (t - 1) & 3 : 0, 1, t * KT, [&](int j) __attribute__((always_inline)) { issue(j); });
+      step(sa, sb, k1, 0, (t - 1) & 3, 1, t * KT, [&](int j) __attribute__((always_inline)) { issue(j); });
       step(sb, sa, k1, 1, t & 3, 0, t * KT + 32, [&](int j) __attribute__((always_inline)) { issue(kSlots + j); });
       vm_wait<kGroup>();
       __syncthreads();

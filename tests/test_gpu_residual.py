@@ -175,3 +175,29 @@ def test_residual_smallest_workspace(monkeypatch):
             assert part < 1.0 and bool((err == -1.0).all())
             continue
         assert float((err / full - 1).abs().max()) < 1e-2
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_vis", [100, 2100])
+def test_residual_infinite_displacement(n_vis, d):
+    """An infinite displacement of one stale token in the second half of the first key tile: infinite errors in its
+    sample and KV head's query heads, and everything else as without it."""
+    hkv, g, n_q, key, head = 2, 7, 30, 40, 1
+    gen = torch.Generator(device=DEV).manual_seed(n_vis + d)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device=DEV).to(torch.bfloat16)
+    n_ctx = n_vis + n_q
+    k, v, q, z = rnd(n_ctx, hkv, d), rnd(n_ctx, hkv, d), rnd(n_q, hkv * g, d), rnd(3, n_vis, hkv, d)
+    kv, img = api.kv_desc(k, v, hkv * g), api.ImageTable(np.array([0], np.int32), np.array([0, n_vis], np.int32))
+    lse = torch.zeros(n_q, hkv * g, device=DEV)
+    s, a = (torch.zeros(n_vis, device=DEV) for _ in range(2))
+    api.conduit_score(kv, q, n_vis, img, s, a, row_lse_out=lse)
+    refreshed = (torch.arange(n_vis, device=DEV) % 7 == 0).to(torch.uint8)
+    errs = []
+    for x in (float(z[1, key, head, 5]), torch.inf):
+        z[1, key, head, 5] = x
+        err = torch.full((3, n_q, hkv * g), -1.0, device=DEV)
+        api.conduit_residual_error(kv, q, n_vis, img, lse, refreshed, err, z=z)
+        errs.append(err)
+    want = errs[0].clone()
+    want[1, :, head * g:(head + 1) * g] = torch.inf
+    assert torch.equal(errs[1], want)

@@ -415,7 +415,13 @@ conduit_status conduit_refresh_attn_layers(const conduit_kv *kvs, int32_t n_laye
  *             kv->dtype, 16-byte aligned.
  * err_out     device [n_samples][n_q][n_q_heads] fp32.
  * ws          256-byte aligned, conduit_residual_workspace_bytes(kv, n_q,
- *             img, n_samples, z != NULL) bytes.
+ *             img, n_samples, z != NULL) bytes.  The visual tokens are summed
+ *             in splits: a workspace of that size or more always takes the
+ *             same split count, so a call repeats its bits.  Where that count
+ *             is above the one whose workgroups fill the chip twice, a smaller
+ *             workspace that holds the latter's partial sums is accepted too
+ *             and takes it (fp32 sums in another order); anything less is
+ *             CONDUIT_ERR_WORKSPACE.
  * Errors: CONDUIT_ERR_INVALID_ARG (NULL row_lse_in / refreshed / err_out,
  * kappa not finite and > 0 with z, n_samples != 1 without z, ...),
  * CONDUIT_ERR_UNSUPPORTED if n_samples * n_kv_heads > 65535.

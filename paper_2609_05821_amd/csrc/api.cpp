@@ -800,11 +800,13 @@ conduit_status conduit_residual_error(const conduit_kv *kv, const void *q, int32
   ImageTable tbl;
   st = check_images(img, q_pos0, &tbl);
   if (st) return st;
-  // (a workspace that holds only the target count's partials takes that count)
-  ResidualLayout L = residual_layout(kv, n_q, img->n_vis, n_samples, iso, true);
-  if (ws_bytes < L.total) L = residual_layout(kv, n_q, img->n_vis, n_samples, iso, false);
-  st = check_ws(ws, ws_bytes, L.total);
+  // The target count's partials are the least that is accepted, whichever
+  // count is the larger; a workspace that holds only them takes that count.
+  const ResidualLayout least = residual_layout(kv, n_q, img->n_vis, n_samples, iso, false);
+  st = check_ws(ws, ws_bytes, least.total);
   if (st) return st;
+  const ResidualLayout rounds = residual_layout(kv, n_q, img->n_vis, n_samples, iso, true);
+  const ResidualLayout &L = ws_bytes >= rounds.total ? rounds : least;
   char *w = static_cast<char *>(ws);
   const bool bf16 = kv->dtype == CONDUIT_BF16;
   ResidualParams rp{};

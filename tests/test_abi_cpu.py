@@ -259,6 +259,24 @@ def test_residual_workspace_sizes():
     assert L.conduit_residual_workspace_bytes(ctypes.byref(kvd), 0, ctypes.byref(IMG.desc), 5, 1) == 0
 
 
+@pytest.mark.parametrize("n_q,n_vis,n_samples,splits,more", [(32, 8192, 5, 16, False), (64, 1024, 5, 2, False),
+                                                             (128, 16384, 5, 8, True), (256, 8192, 5, 4, True)])
+def test_residual_least_workspace(n_q, n_vis, n_samples, splits, more):
+    """The least accepted workspace holds the partial sums of the split count whose workgroups fill the chip twice
+    (8 to 32 key tiles a split), whether the preferred count needs less or, `more`, more than that."""
+    img = api.ImageTable([0], [0, n_vis])
+    kvd = kv(n_ctx=n_vis + n_q)
+    up = lambda b: -(-b // 256) * 256
+    blocks = -(-n_q * 7 // 256) * 4 * n_samples
+    assert splits == max(min(-(-512 // blocks), n_vis // 64 // 8), n_vis // 64 // 32)
+    least = up(n_q * 28 * 4) + up(n_vis * 4) + n_samples * splits * 4 * (-(-n_q * 7 // 256) * 256) * 128 * 4
+    need = api.lib().conduit_residual_workspace_bytes(ctypes.byref(kvd), n_q, ctypes.byref(img.desc), n_samples, 1)
+    assert need > least if more else need == least
+    for ws_bytes in (least - 1, least * 3 // 4, 0):
+        assert residual(kvd=kvd, n_q=n_q, q_pos0=n_vis, img=img, n_samples=n_samples,
+                        ws_bytes=ws_bytes) == api.ERR_WORKSPACE
+
+
 def test_ceiling_reference_library():
     """The benchmark's matrix-core reference (a separate library, not part of
     the C ABI): it loads, sizes its operands and counts its FLOP without a

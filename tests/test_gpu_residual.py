@@ -151,30 +151,37 @@ def test_residual_tile_pipeline(n_vis, d):
         assert_scores(to_f64(got), ref, rtol=rtol(w), what="err")
 
 
-def test_residual_smallest_workspace(monkeypatch):
-    """Split counts depend on the workspace given (the full size, and less): the errors agree, and a workspace below
-    the least one is refused.  A split rounds its weights the same way whatever the count, so the entries differ by
-    fp32 sums only; the bound is half the one against the oracle."""
-    w = W.custom(1, 28, 4, 128, 32, 3, [1024] * 8, 2, "bf16", n_relevant=1, seed=31)
-    L = w.layer(0, fresh=False)
-    k, v, q = (to_dev(L[x]) for x in ("k", "v", "q"))
-    kv = api.kv_desc(k, v, w.n_q_heads)
-    img = api.ImageTable(w.img_pos, w.img_off)
-    lse = row_lse(w, kv, q, img, O.NORM_CAUSAL_ROW)
-    refreshed = to_dev((np.arange(w.n_vis) % 7 == 0).astype(np.uint8))
-    z = to_dev(W.iso_directions(w, 0, M))
-    full = run(w, kv, q, img, lse, refreshed, z)
-    need = api.residual_workspace_bytes(kv, w.n_q, img, M, True)
-    monkeypatch.setattr(api, "_workspace", lambda nbytes, device, ws: ws)
-    for part in (1.0, 0.95, 0.9, 0.5):
-        err = torch.full_like(full, -1.0)
-        ws = torch.empty(int(need * part), dtype=torch.uint8, device=DEV)
-        try:
-            api.conduit_residual_error(kv, q, w.q_pos0, img, lse, refreshed, err, z=z, ws=ws)
-        except api.ConduitError:
-            assert part < 1.0 and bool((err == -1.0).all())
-            continue
-        assert float((err / full - 1).abs().max()) < 1e-2
+@pytest.mark.parametrize("n_q,n_vis,splits", [(128, 16384, 8), (256, 8192, 4)])
+def test_residual_smallest_workspace(n_q, n_vis, splits):
+    """The workspace query covers a split count above the one that fills the chip twice (`splits` of them): a
+    workspace that holds just the latter's partial sums is accepted and takes it, one byte less is refused.  The
+    products and weights are the same bits either way, and a displacement sum of N = n_vis terms in fp32 in another
+    order moves by about sqrt(N) 2^-24 relative: twice that in its squared norm, at most 1.6e-5."""
+    hkv, g, d = 4, 7, 128
+    gen = torch.Generator(device=DEV).manual_seed(n_vis)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device=DEV).to(torch.bfloat16)
+    n_ctx = n_vis + n_q
+    k, v, q, z = rnd(n_ctx, hkv, d), rnd(n_ctx, hkv, d), rnd(n_q, hkv * g, d), rnd(M, n_vis, hkv, d)
+    kv, img = api.kv_desc(k, v, hkv * g), api.ImageTable(np.array([0], np.int32), np.array([0, n_vis], np.int32))
+    lse = torch.zeros(n_q, hkv * g, device=DEV)
+    s, a = (torch.zeros(n_vis, device=DEV) for _ in range(2))
+    api.conduit_score(kv, q, n_vis, img, s, a, row_lse_out=lse)
+    refreshed = (torch.arange(n_vis, device=DEV) % 7 == 0).to(torch.uint8)
+    pad = -(-n_q * g // 256) * 256  # (row, head) pairs of a KV head, whole blocks
+    least = n_q * hkv * g * 4 + n_vis * 4 + M * splits * hkv * pad * d * 4
+    need = api.residual_workspace_bytes(kv, n_q, img, M, True)
+    assert need > least
+    errs = []
+    for nbytes in (need, 2 * need, least):
+        err = torch.full((M, n_q, hkv * g), -1.0, device=DEV)
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+        api.conduit_residual_error(kv, q, n_vis, img, lse, refreshed, err, z=z, ws=ws)
+        errs.append(err)
+    assert torch.equal(errs[0], errs[1])
+    assert not torch.equal(errs[0], errs[2])
+    assert float((errs[2] / errs[0] - 1).abs().max()) < 2e-5
+    with pytest.raises(api.ConduitError):
+        api.conduit_residual_error(kv, q, n_vis, img, lse, refreshed, errs[0], z=z, ws=ws[:least - 1])
 
 
 @pytest.mark.parametrize("d", [64, 128])

@@ -497,7 +497,6 @@ conduit_status conduit_score(const conduit_kv *kv, const void *q, int32_t n_q, i
     cs.lse_part_m = reinterpret_cast<float *>(at(ws, L.plan.part_m));
     cs.lse_part_l = reinterpret_cast<float *>(at(ws, L.plan.part_l));
     cs.lse_ns = lse_ns;
-    cs.lse_ppb = attn_pairs_per_block(false);
     cs.lse_out = row_lse_out;
   } else if (bf16 && !row_lse_in) {
     cs.clear_u32 = reinterpret_cast<uint32_t *>(at(ws, L.merge_flag));
@@ -655,7 +654,6 @@ conduit_status conduit_score_layers(const conduit_kv *kvs, int32_t n_layers, con
     cs.lse_part_m = merge_lse ? ap.part_m : nullptr;
     cs.lse_part_l = merge_lse ? ap.part_l : nullptr;
     cs.lse_ns = merge_lse ? lse_ns : 0;
-    cs.lse_ppb = merge_lse ? attn_pairs_per_block(false) : 0;
     cs.lse_layer_stride = merge_lse ? (int64_t)L.plan.max_items * attn_pairs_per_block(false) : 0;
     hipError_t e = launch_attn(ap, D, false, stream, &lt);
     if (e != hipSuccess) return hip_fail(e, "row statistics");

@@ -435,10 +435,10 @@ struct ColsumParams {
   float *lse_out;           // natural log
   // bf16, launches of 8-wave workgroups: row log-sum-exps merged by every
   // workgroup from the statistics' split partials (lse_ns <= kLseRegSplits
-  // splits of lse_ppb-pair blocks) instead of read from row_b; nullable.
+  // splits of attn_pairs_per_block(false)-pair blocks) instead of read from
+  // row_b; nullable.
   const float *lse_part_m;
   const float *lse_part_l;
-  int32_t lse_ppb;
   int64_t lse_layer_stride;  // partials per layer of a multi-layer launch
   uint32_t *clear_u32;      // nullable: [clear_n] words cleared by the kernel (bf16)
   int32_t clear_n;

@@ -136,11 +136,10 @@ constexpr int kMergeLoads = 6;   // splits asked for together
 template <int D, bool MERGE>
 struct ColsumSmem {
   alignas(16) u16 q[kQStages][kQTile][D + 8];
-  // MERGE: every row's (and two tiles that are read ahead), else a ring
-  alignas(16) float nb[MERGE ? kColsumMaxLsePairs / kQTile + 2 : kBTiles][kQTile];  // -b of the tiles' rows (doubled for RMS; past the last row: -inf)
+  // MERGE: every row's, else a ring
+  alignas(16) float nb[MERGE ? kColsumMaxLsePairs / kQTile : kBTiles][kQTile];  // -b of the tiles' rows (doubled for RMS; past the last row: -inf)
   uint32_t off[kBTiles][kQTile];          // byte offsets of the tiles' rows
   int64_t row[kColsumKeysPerBlock];       // cache row of each key of the workgroup
-  float part[kColsumKeysPerBlock];        // RH = 2: column sums of the odd row halves
   ImageLds img;
 };
 
@@ -149,30 +148,39 @@ struct ColsumSmem {
 // lt.n > 0: several layers, layer blockIdx.z (the column sums and norms of
 // layer l sit l strides further on).
 //
-// A workgroup covers 256 keys; every wave holds the K rows of 64 of them, so
-// that each Q operand read from LDS feeds two products.  RH = 1: 4 waves, each
-// takes every row, two workgroups per CU, so that one's start and end (K rows,
-// norms, the finalize handoff: about 8 us against 25 of the loop at 1,792
-// rows) run beside the other's loop.  RH = 2 (launches whose workgroups do not
-// fill the chip twice): 8 waves, wave w takes the 32-row half w / 4 of every
-// tile.  The loop runs over 32-row sub-tiles i with one product per slot:
-// S(i+1) = Q K^T from the operand ring while 2^(c S(i) - b) is summed on the
-// VALU and the ring receives the operands of i + 2.  It is bound by
-// instruction issue (a product with 2 exponentials, 2 FMAs and 2 additions
-// takes 42 cycles at two waves per SIMD, each LDS read about 13 more, the
-// product alone 32): 66 cycles per product over the whole kernel at 65,536
-// keys x 1,792 rows x 4 layers (0.94 M; 1.40 M with 32 keys per wave, operands
-// read one product ahead and one 8-wave workgroup per CU).
-// MERGE (RH = 2 only): the rows' b are merged from the statistics' split
+// A workgroup covers 256 keys; every wave holds the K rows of 32 NC of them and
+// takes every row.  The loop runs over 32-row sub-tiles i with one product per
+// slot: S(i+1) = Q K^T from the operand ring while 2^(c S(i) - b) is summed on
+// the VALU and the ring receives the operands of i + 2; the last pair of tiles
+// stands behind the loop, without transfers, and its last sub-tile without
+// products.  The loop is bound by instruction issue (a product with 2
+// exponentials, 2 FMAs and 2 additions takes 42 cycles at two waves per SIMD,
+// each LDS read about 13 more, the product alone 32).
+// NC = 2: 4 waves, each Q operand read from LDS feeds two products, and two
+// workgroups per CU, so that one's start and end (K rows, norms, the finalize
+// handoff: about 8 us against 25 of the loop at 1,792 rows) run beside the
+// other's loop.  65,536 keys x 1,792 rows x 4 layers take 66 cycles per product
+// over the whole kernel.
+// NC = 1 (launches whose workgroups do not fill the chip twice): 8 waves, for
+// start and end count there, and with 32 keys a wave asks for half the K rows
+// and has half the products before its first sum.  A form with 64 keys and one
+// row half of every tile per wave fetched each K row twice: whole scoring
+// passes with given row statistics, that form and this one, 27.0 and 25.1 us
+// (16,384 keys x 896 rows), 14.5 and 13.2 (1,892 x 119); d = 64, 38,087 x 161
+// rows without, 37.9 and 31.6 (two workgroups per CU where the registers of d =
+// 64 allow it).
+// MERGE (NC = 1 only): the rows' b are merged from the statistics' split
 // partials by every workgroup, asked for at its start and reduced after the K
 // rows have been asked for, in place of the statistics kernel's merge, whose
-// chain of waits at its end costs about 4 us (16k scoring 0.985 of the 32-key
-// kernels' speed with that merge, 1.018 with this one; a single-image step
-// 71.6 and 69.6 us).
-template <int D, int RH, bool MERGE>
-__global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumParams p, LayerTable lt, int rms) {
+// chain of waits at its end costs about 4 us (16k scoring 49.6 us with this
+// merge and 54.0 with that one and 4 waves).  Rows and splits that there are
+// not are left out (3,244 keys x 161 rows, 7 splits: 14.3 us with all 24 splits
+// of two rows per thread reduced, 12.8 now).
+template <int D, int NC, bool MERGE>
+__global__ __launch_bounds__(512 / NC, NC == 1 && D == 64 && !MERGE ? 4 : 2) void colsum_bf16_kernel(
+    ColsumParams p, LayerTable lt, int rms) {
   constexpr int KS = D / 16;
-  constexpr int kThreads = 256 * RH, W = kThreads / 64;
+  constexpr int W = 8 / NC, kThreads = 64 * W;
   // The parameter block is read in one go: the empty statement makes every
   // scalar due here, otherwise each is loaded where it is first used, a chain
   // of about a dozen round trips before the first product.  The image table's
@@ -184,8 +192,7 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
                "s"(p.n_kv_heads), "s"(p.group), "s"(p.n_q_heads), "s"(p.n_q), "s"(p.n_vis), "s"(p.scale_log2),
                "s"(p.clear_u32), "s"(p.clear_n), "s"(p.done), "s"(p.tbl.n_images), "s"(lt.n));
   if constexpr (MERGE)
-    asm volatile("" ::"s"(p.lse_part_m), "s"(p.lse_part_l), "s"(p.lse_ns), "s"(p.lse_ppb), "s"(p.lse_layer_stride),
-                 "s"(p.lse_out));
+    asm volatile("" ::"s"(p.lse_part_m), "s"(p.lse_part_l), "s"(p.lse_ns), "s"(p.lse_layer_stride), "s"(p.lse_out));
   // This layer's pointers, in locals: p itself stays unwritten (a written
   // kernel parameter holding the image table would be copied to scratch).
   const bool ml = lt.n > 0;
@@ -203,7 +210,7 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int col = lane & 31, half = lane >> 5;
-  const int key0 = (wave & 3) * 64, wsub = wave >> 2;
+  const int key0 = wave * 32 * NC;
   const int blk_key0 = blockIdx.x * kColsumKeysPerBlock;
   const int kvh = blockIdx.y;
   const int G = p.group;
@@ -303,25 +310,25 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
   // until the K rows have been asked for.
   float b_first = 0.f;
   // MERGE: b = M + log2(sum_s l_s 2^(m_s - M)) over the splits of a row, in
-  // split order, kMergeRows rows r0 + tid + i kThreads per thread; the first
-  // key block also writes lse_out.  Slot (pb n_kv_heads + kvh) ns + s holds
-  // split s of the rows of block pb.
+  // split order, kMergeRows rows r0 + tid + i kThreads per thread (as far as
+  // there are any), kMergeLoads splits in one go (as far as there are any);
+  // the first key block also writes lse_out.  Slot (pb n_kv_heads + kvh) ns + s
+  // holds split s of the rows of block pb.
   float mv[kMergeRows][MERGE ? kLseRegSplits : 1], lv[kMergeRows][MERGE ? kLseRegSplits : 1];
   auto ask_rows = [&](int r0) __attribute__((always_inline)) {
+    constexpr int ppb = attn_pairs_per_block(false);
     const float *pm = p.lse_part_m + layer * p.lse_layer_stride, *pl = p.lse_part_l + layer * p.lse_layer_stride;
 #pragma unroll
     for (int i = 0; i < kMergeRows; ++i) {
-      const int r = min(r0 + tid + i * kThreads, n_pair - 1);
-      const int pb = r / p.lse_ppb;
-      const int64_t at = ((int64_t)pb * p.n_kv_heads + kvh) * p.lse_ns * p.lse_ppb + (r - pb * p.lse_ppb);
+      if (i > 0 && r0 + i * kThreads >= n_pair) break;
+      const uint32_t r = (uint32_t)min(r0 + tid + i * kThreads, n_pair - 1), pb = r / ppb;
+      const int64_t at = ((int64_t)pb * p.n_kv_heads + kvh) * p.lse_ns * ppb + (r - pb * ppb);
 #pragma unroll
       for (int s0 = 0; s0 < kLseRegSplits; s0 += kMergeLoads) {
-#pragma unroll
-        for (int u = 0; u < kMergeLoads; ++u) mv[i][s0 + u] = -kInf, lv[i][s0 + u] = 0.f;
         if (s0 < p.lse_ns) {
 #pragma unroll
           for (int u = 0; u < kMergeLoads; ++u) {
-            const int64_t e = at + (int64_t)min(s0 + u, p.lse_ns - 1) * p.lse_ppb;
+            const int64_t e = at + (int64_t)min(s0 + u, p.lse_ns - 1) * ppb;
             mv[i][s0 + u] = pm[e];
             lv[i][s0 + u] = pl[e];
           }
@@ -332,12 +339,22 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
   auto merge_rows = [&](int r0) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < kMergeRows; ++i) {
+      if (i > 0 && r0 + i * kThreads >= n_pair) break;
       const int r = r0 + tid + i * kThreads;
       float M = mv[i][0], L = 0.f;
 #pragma unroll
-      for (int u = 1; u < kLseRegSplits; ++u) M = fmaxf(M, mv[i][u]);  // (clamped loads repeat the last split)
+      for (int s0 = 0; s0 < kLseRegSplits; s0 += kMergeLoads)
+        if (s0 < p.lse_ns) {
 #pragma unroll
-      for (int u = 0; u < kLseRegSplits; ++u) L += u < p.lse_ns ? fast_exp2(mv[i][u] - M) * lv[i][u] : 0.f;
+          for (int u = 0; u < kMergeLoads; ++u) M = fmaxf(M, mv[i][s0 + u]);  // (clamped loads repeat the last split)
+        }
+#pragma unroll
+      for (int s0 = 0; s0 < kLseRegSplits; s0 += kMergeLoads)
+        if (s0 < p.lse_ns) {
+#pragma unroll
+          for (int u = 0; u < kMergeLoads; ++u)
+            L += s0 + u < p.lse_ns ? fast_exp2(mv[i][s0 + u] - M) * lv[i][s0 + u] : 0.f;
+        }
       const float b = M + __log2f(L);
       if (r < n_tiles * kQTile) nb[r] = neg_b(b, r);
       if (p.lse_out && !ml && blockIdx.x == 0 && r < n_pair)
@@ -369,42 +386,43 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
     sm.img.n_images = p.tbl.n_images;
   }
   __syncthreads();
-  // tiles 0 and 1, and 2 (RH = 1: the first iteration takes 3) or 2 and 3
+  // tiles 0, 1 and 2 (the first iteration takes 3)
   each([&](auto n) __attribute__((always_inline)) { dma_q(n, sm.off[0], sm.off[1], q_lds, q_lds + kStageB); });
   // (a span of one or two tiles uses nothing of what it reads from them)
   if (n_tiles > 2)
     each([&](auto n) __attribute__((always_inline)) {
-      if (RH == 2 || (decltype(n)::value < 2 * kFull ? decltype(n)::value % 2 == 0 : !left_b))
+      if (decltype(n)::value < 2 * kFull ? decltype(n)::value % 2 == 0 : !left_b)
         dma_q(n, sm.off[2], sm.off[3], q_lds + 2 * kStageB, q_lds + 3 * kStageB);
     });
 
   // This lane's key columns, held as the B operands for every row tile.
-  bf16x8 kreg[2][KS];
+  bf16x8 kreg[NC][KS];
   {
     // the keys' cache rows (page lookup included), also kept for the V rows;
-    // both searches of the image table step together
-    int tk[2], lo[2] = {0, 0}, hi[2];
+    // the searches of the image table step together
+    int tk[NC], lo[NC], hi[NC];
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb) {
+    for (int cb = 0; cb < NC; ++cb) {
       tk[cb] = min(blk_key0 + key0 + cb * 32 + col, p.n_vis - 1);
+      lo[cb] = 0;
       hi[cb] = sm.img.n_images - 1;
     }
-    while (lo[0] < hi[0] || lo[1] < hi[1]) {
+    while (lo[0] < hi[0] || lo[NC - 1] < hi[NC - 1]) {
 #pragma unroll
-      for (int cb = 0; cb < 2; ++cb) {
+      for (int cb = 0; cb < NC; ++cb) {
         const int mid = (lo[cb] + hi[cb] + 1) >> 1;
         const bool up = sm.img.off[mid] <= tk[cb];
         lo[cb] = up ? mid : lo[cb];  // lo = hi stays: its offset is at most tk
         hi[cb] = up ? hi[cb] : mid - 1;
       }
     }
-    int64_t row[2];
+    int64_t row[NC];
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb)
+    for (int cb = 0; cb < NC; ++cb)
       row[cb] = kv_row(p.pages, sm.img.pos[lo[cb]] + (tk[cb] - sm.img.off[lo[cb]]));
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb) {
-      if (half == 0 && wsub == 0) sm.row[key0 + cb * 32 + col] = row[cb];
+    for (int cb = 0; cb < NC; ++cb) {
+      if (half == 0) sm.row[key0 + cb * 32 + col] = row[cb];
       const u16 *krow = Kg + row[cb] * p.k_stride + kvh * D + 8 * half;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) kreg[cb][ks] = as_bf16x8(ld16(krow + ks * 16));
@@ -422,49 +440,53 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
   __builtin_amdgcn_s_waitcnt(0);  // this wave's Q transfers (invisible to the compiler)
   __syncthreads();
 
-  // S of sub-tile 0, the operands of sub-tile 1 (RH = 2: of the next tile).
+  // S of sub-tile 0, the operands of sub-tile 1.
   bf16x8 ring[KS];
-  f32x16 sa[2], sb[2];
+  f32x16 sa[NC], sb[NC];
   {
-    const u16 *qrow = &sm.q[0][32 * wsub + col][8 * half];
+    const u16 *qrow = &sm.q[0][col][8 * half];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) ring[ks] = as_bf16x8(ld16(qrow + ks * 16));
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb) {
+    for (int cb = 0; cb < NC; ++cb) {
       sa[cb] = f32x16{};
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
         sa[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[ks], kreg[cb][ks], sa[cb], 0, 0, 0);
     }
-    const u16 *qnext = RH == 1 ? qrow + 32 * (D + 8) : qrow + kQTile * (D + 8);
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) ring[ks] = as_bf16x8(ld16(qnext + ks * 16));
+    for (int ks = 0; ks < KS; ++ks) ring[ks] = as_bf16x8(ld16(qrow + 32 * (D + 8) + ks * 16));
   }
   __syncthreads();  // every wave has read these tiles: the first iteration refills their stages
 
-  float colsum[2] = {0.f, 0.f};
-  constexpr int kVPer = 16 / (2 * KS);  // accumulator registers (of both columns) per slot
+  float colsum[NC] = {};
+  constexpr int kVPer = 16 / (NC * KS);  // accumulator registers (of every column) per slot
   // -b of the rows of sub-tile `sub` of a tile that this lane holds: register
   // v of lane (col, half) is row 8*(v/4) + 4*half + v%4 of its sub-tile
   auto b_of = [&](int tile, int sub) __attribute__((always_inline)) {
     return nb + (MERGE ? tile : tile & (kBTiles - 1)) * kQTile + 32 * sub + 4 * half;
   };
-  f32x4 nb4 = *reinterpret_cast<const f32x4 *>(b_of(0, wsub));  // rows 0..3 of the current sub-tile
-  // One sub-step: cur = S(i), with b at bp; nxt receives S(i+1) from the
-  // ring, the ring rows qsub * 32.. of stage qst; bn: b of sub-tile i + 1.
-  auto step = [&](f32x16 (&cur)[2], f32x16 (&nxt)[2], int qst, int qsub, const float *bp, const float *bn,
-                  auto hook) __attribute__((always_inline)) {
+  f32x4 nb4 = *reinterpret_cast<const f32x4 *>(b_of(0, 0));  // rows 0..3 of the current sub-tile
+  // One sub-step: cur = S(i), with b at bp; nxt receives S(i+1) from the ring
+  // (Ops >= 1), the ring rows qsub * 32.. of stage qst (Ops = 2); bn: b of
+  // sub-tile i + 1.
+  auto step = [&](auto ops_tag, f32x16 (&cur)[NC], f32x16 (&nxt)[NC], int qst, int qsub, const float *bp,
+                  const float *bn, auto hook) __attribute__((always_inline)) {
+    constexpr int Ops = decltype(ops_tag)::value;
     const u16 *qrow = &sm.q[qst][32 * qsub + col][8 * half];
     f32x4 nbn = nb4;
-    float last[2] = {0.f, 0.f}, psum[2] = {0.f, 0.f};
+    float last[NC] = {}, psum[NC] = {};
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < 2 * KS; ++j) {
-      const int op = j / 2, cb = j % 2;
-      nxt[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[op], kreg[cb][op], op == 0 ? f32x16{} : nxt[cb], 0, 0, 0);
-      if (cb == 1 && (op & 1)) {
-        ring[op] = as_bf16x8(ld16(qrow + op * 16));
-        ring[op - 1] = as_bf16x8(ld16(qrow + (op - 1) * 16));
+    for (int j = 0; j < NC * KS; ++j) {
+      const int op = j / NC, cb = j % NC;
+      if constexpr (Ops >= 1)
+        nxt[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[op], kreg[cb][op], op == 0 ? f32x16{} : nxt[cb], 0, 0, 0);
+      if constexpr (Ops == 2) {
+        if (cb == NC - 1 && (op & 1)) {
+          ring[op] = as_bf16x8(ld16(qrow + op * 16));
+          ring[op - 1] = as_bf16x8(ld16(qrow + (op - 1) * 16));
+        }
       }
 #pragma unroll
       for (int v = j * kVPer; v < (j + 1) * kVPer; ++v) {
@@ -473,7 +495,7 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
           nbn = *reinterpret_cast<const f32x4 *>(v < 12 ? bp + 8 * (v / 4 + 1) : bn);
         }
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < NC; ++u) {
           const float pe = fast_exp2(fmaf(cur[u][v], c, nb4[v % 4]));
           asm volatile("" ::"v"(pe));
           psum[u] += last[u];
@@ -482,20 +504,24 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
         }
       }
       hook(j);
-      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (Ops >= 1) __builtin_amdgcn_sched_barrier(0);
     }
     nb4 = nbn;
-    colsum[0] += psum[0] + last[0];
-    colsum[1] += psum[1] + last[1];
-    asm volatile("" ::"v"(colsum[0]), "v"(colsum[1]));
+#pragma unroll
+    for (int u = 0; u < NC; ++u) {
+      colsum[u] += psum[u] + last[u];
+      asm volatile("" ::"v"(colsum[u]));
+    }
   };
-  // Two tiles (t, t+1) per barrier.  RH = 1 reads tiles t+1, t+2 while t+3,
-  // t+4 arrive; RH = 2 (one sub-tile of each) reads t+2, t+3 while t+4, t+5
-  // arrive.
+  constexpr std::integral_constant<int, 0> kSumOnly{};
+  constexpr std::integral_constant<int, 1> kNoRead{};
+  constexpr std::integral_constant<int, 2> kAll{};
+  auto no_hook = [](int) __attribute__((always_inline)) {};
   // V rows of the workgroup's keys for the value norms (not read when the
   // norms are given), kVBatch 16-byte pieces per thread at a time; the first
   // batch arrives during the last but one iteration.
   const bool read_v = vnorm_in == nullptr;
+  constexpr bool kVEarly = NC == 1;
   constexpr int VPT = kColsumKeysPerBlock * D / 8 / kThreads, kVBatch = VPT < 8 ? VPT : 8;
   u32x4 vv[kVBatch] = {};
   auto load_v = [&](int i0) __attribute__((always_inline)) {
@@ -505,20 +531,23 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
       vv[i] = ld16(Vg + sm.row[vi / (D / 8)] * p.v_stride + kvh * D + (vi % (D / 8)) * 8);
     }
   };
-  const int v_at = max(((n_tiles - 1) & ~1) - 2, 0);
+  // Two tiles (t, t+1) per barrier while two more follow: reads tiles t+1,
+  // t+2 while t+3, t+4 arrive.
+  const int t_last = (n_tiles - 1) & ~1;  // the last pair (its second tile may not exist)
   constexpr int kMod = kBTiles - 1;
-  for (int t = 0, st = 0; t < n_tiles; t += 2, st ^= 2) {
+  int t = 0, st = 0;
+  for (; t < t_last; t += 2, st ^= 2) {
     const int s1 = st + 1, s2 = st ^ 2, s3 = (st ^ 2) + 1;  // stages of t+1, t+2, t+3
-    constexpr int kStep = 2 * KS, kSpread = (RH == 1 ? 4 : 2) * kStep / kGroup;
+    constexpr int kStep = NC * KS, kSpread = 4 * kStep / kGroup;
     static_assert(kSpread >= 1, "every transfer has a slot");
-    const uint32_t *off_a = sm.off[(t + 4) & kMod], *off_b = sm.off[(t + (RH == 1 ? 3 : 5)) & kMod];
-    const uint32_t s_a = q_lds + st * kStageB, s_b = q_lds + (RH == 1 ? s3 : s1) * kStageB;
+    const uint32_t *off_a = sm.off[(t + 4) & kMod], *off_b = sm.off[(t + 3) & kMod];
+    const uint32_t s_a = q_lds + st * kStageB, s_b = q_lds + s3 * kStageB;
     auto slot = [&](int g) __attribute__((always_inline)) {
       each([&](auto n) __attribute__((always_inline)) {
         if (g == decltype(n)::value * kSpread) dma_q(n, off_a, off_b, s_a, s_b);
       });
     };
-    if (read_v && t == v_at) load_v(0);
+    if (kVEarly && read_v && t == t_last - 2) load_v(0);
     // -b of the rows of tiles t+4, t+5 and the offsets of t+6, t+7
     float bv = 0.f;
     if (wave < 2) {
@@ -526,40 +555,33 @@ __global__ __launch_bounds__(256 * RH, 3 - RH) void colsum_bf16_kernel(ColsumPar
       next_rows();
       sm.off[(t + 6) & kMod][tid] = row_off();
     }
-    if constexpr (RH == 1) {
-      step(sa, sb, s1, 0, b_of(t, 0), b_of(t, 1), [&](int j) __attribute__((always_inline)) { slot(j); });
-      step(sb, sa, s1, 1, b_of(t, 1), b_of(t + 1, 0), [&](int j) __attribute__((always_inline)) { slot(kStep + j); });
-      if (t + 1 < n_tiles) {
-        step(sa, sb, s2, 0, b_of(t + 1, 0), b_of(t + 1, 1),
-             [&](int j) __attribute__((always_inline)) { slot(2 * kStep + j); });
-        step(sb, sa, s2, 1, b_of(t + 1, 1), b_of(t + 2, 0),
-             [&](int j) __attribute__((always_inline)) { slot(3 * kStep + j); });
-      }
-    } else {
-      step(sa, sb, s2, wsub, b_of(t, wsub), b_of(t + 1, wsub), [&](int j) __attribute__((always_inline)) { slot(j); });
-      if (t + 1 < n_tiles)
-        step(sb, sa, s3, wsub, b_of(t + 1, wsub), b_of(t + 2, wsub),
-             [&](int j) __attribute__((always_inline)) { slot(kStep + j); });
-    }
+    step(kAll, sa, sb, s1, 0, b_of(t, 0), b_of(t, 1), [&](int j) __attribute__((always_inline)) { slot(j); });
+    step(kAll, sb, sa, s1, 1, b_of(t, 1), b_of(t + 1, 0), [&](int j) __attribute__((always_inline)) { slot(kStep + j); });
+    step(kAll, sa, sb, s2, 0, b_of(t + 1, 0), b_of(t + 1, 1),
+         [&](int j) __attribute__((always_inline)) { slot(2 * kStep + j); });
+    step(kAll, sb, sa, s2, 1, b_of(t + 1, 1), b_of(t + 2, 0),
+         [&](int j) __attribute__((always_inline)) { slot(3 * kStep + j); });
     if (!MERGE && wave < 2) sm.nb[(t + 4) & kMod][tid] = neg_b(bv, (t + 4) * kQTile + tid);
     __builtin_amdgcn_s_waitcnt(0);  // this wave's transfers have landed
     __syncthreads();
   }
-
-  // The lanes' halves of a key's rows, then (RH = 2) the row halves.
-#pragma unroll
-  for (int cb = 0; cb < 2; ++cb) {
-    colsum[cb] += __shfl_xor(colsum[cb], 32, 64);
-    if (RH == 2 && wsub == 1 && half == 0) sm.part[key0 + cb * 32 + col] = colsum[cb];
+  // The last one or two tiles: everything they need is there.
+  if (read_v && (!kVEarly || t_last == 0)) load_v(0);
+  const bool pair = t + 1 < n_tiles;
+  if (pair) {
+    step(kAll, sa, sb, st + 1, 0, b_of(t, 0), b_of(t, 1), no_hook);
+    step(kAll, sb, sa, st + 1, 1, b_of(t, 1), b_of(t + 1, 0), no_hook);
   }
-  if (RH == 2) __syncthreads();
-  if (wsub == 0 && half == 0) {
+  const float *b0 = b_of(pair ? t + 1 : t, 0), *b1 = b_of(pair ? t + 1 : t, 1);
+  step(kNoRead, sa, sb, 0, 0, b0, b1, no_hook);
+  step(kSumOnly, sb, sa, 0, 0, b1, b1, no_hook);
+
+  // The lanes' halves of a key's rows.
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb) {
-      const int i = key0 + cb * 32 + col, t = blk_key0 + i;
-      if (RH == 2) colsum[cb] += sm.part[i];
-      if (t < p.n_vis) store_coherent(colsum_part + (int64_t)kvh * p.n_vis + t, colsum[cb]);
-    }
+  for (int cb = 0; cb < NC; ++cb) {
+    colsum[cb] += __shfl_xor(colsum[cb], 32, 64);
+    const int tk = blk_key0 + key0 + cb * 32 + col;
+    if (half == 0 && tk < p.n_vis) store_coherent(colsum_part + (int64_t)kvh * p.n_vis + tk, colsum[cb]);
   }
 
   // Value-norm proxy: this head's share of ||V_t||^2.  Item vi covers
@@ -731,17 +753,20 @@ hipError_t launch_colsum(const ColsumParams &p, int head_dim, bool bf16, bool rm
   if (bf16) {
     const dim3 grid((p.n_vis + kColsumKeysPerBlock - 1) / kColsumKeysPerBlock, p.n_kv_heads, lt0.n > 0 ? lt0.n : 1);
     // Two 4-wave workgroups per CU when the launch has that many, else 8-wave
-    // ones (4-layer document: 688 us with 8 waves, 573 with 4; one 16k layer,
-    // one workgroup per CU: 25 us with 8 waves, a wave per SIMD idles with 4).
+    // ones: scoring with given row statistics, 8 and 4 waves, 128 rows x 28
+    // heads at d = 128: 24.7 and 25.2 us with 256 workgroups, 55.1 and 48.8
+    // with 564; d = 64, 16 heads: 16.2 and 16.9 with 256, 19.9 and 20.3 with
+    // 440, 25.1 and 24.6 with 564.  (Between 257 and 511 workgroups d = 128
+    // runs two rounds of 8-wave ones, 39.9 us with 440 against 35.3.)
     const bool two = colsum_blocks(p.n_vis, p.n_kv_heads, lt0.n > 0 ? lt0.n : 1) >= kColsumFourWaveBlocks;
     if (p.lse_part_m && (two || p.lse_ns > kLseRegSplits || (int64_t)p.n_q * p.group > kColsumMaxLsePairs))
       return hipErrorInvalidValue;
     ProfScope ps("colsum", s);
     auto launch = [&](auto d) {
       constexpr int D = decltype(d)::value;
-      if (two) colsum_bf16_kernel<D, 1, false><<<grid, 256, 0, s>>>(p, lt0, rms);
-      else if (p.lse_part_m) colsum_bf16_kernel<D, 2, true><<<grid, 512, 0, s>>>(p, lt0, rms);
-      else colsum_bf16_kernel<D, 2, false><<<grid, 512, 0, s>>>(p, lt0, rms);
+      if (two) colsum_bf16_kernel<D, 2, false><<<grid, 256, 0, s>>>(p, lt0, rms);
+      else if (p.lse_part_m) colsum_bf16_kernel<D, 1, true><<<grid, 512, 0, s>>>(p, lt0, rms);
+      else colsum_bf16_kernel<D, 1, false><<<grid, 512, 0, s>>>(p, lt0, rms);
     };
     if (head_dim == 128) launch(std::integral_constant<int, 128>{});
     else launch(std::integral_constant<int, 64>{});

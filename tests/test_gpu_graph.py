@@ -60,3 +60,52 @@ def test_graph_replays_equal_eager(cfg):
         restore()
         one_step()  # eager work between replays
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("n_q,hkv,g,d,n_vis,layers", [(20, 8, 2, 64, 16500, 1), (8, 4, 7, 128, 16384, 1),
+                                                      (40, 4, 3, 128, 4200, 9), (24, 4, 2, 64, 2000, 18)])
+def test_graph_replays_of_merging_statistics(n_q, hkv, g, d, n_vis, layers):
+    """Scoring whose statistics kernel merges its own split rows (512 or more column-sum workgroups, more splits than
+    the column sums merge, several launches of layers), captured and replayed back to back on new keys and queries
+    with nothing else on its workspace: each replay gives the eager call's bits, and the merge marks, the last part
+    of the workspace, are unset again after it."""
+    gen = torch.Generator(device=DEV).manual_seed(n_vis + layers)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device=DEV).to(torch.bfloat16)
+    q_pos0, n_ctx = 7 + n_vis, 7 + n_vis + n_q
+    L = [(rnd(n_ctx, hkv, d), rnd(n_ctx, hkv, d), rnd(n_q, hkv * g, d)) for _ in range(layers)]
+    kvs, qs = [api.kv_desc(k, v, hkv * g) for k, v, _ in L], [q for _, _, q in L]
+    img = api.ImageTable(np.array([5], np.int32), np.array([0, n_vis], np.int32))
+    lse = torch.zeros(n_q, hkv * g, device=DEV)
+    s, a = (torch.zeros(n_vis, device=DEV) for _ in range(2))
+    need = (api.score_workspace_bytes(kvs[0], n_q, img) if layers == 1
+            else api.score_layers_workspace_bytes(kvs[0], n_q, img, layers))
+    ws, ws_eager = (torch.full((need // 4,), 0x5a5a5a5a, dtype=torch.int32, device=DEV) for _ in range(2))
+
+    def score(w):
+        if layers == 1:
+            api.conduit_score(kvs[0], qs[0], q_pos0, img, s, a, row_lse_out=lse, ws=w)
+        else:
+            api.conduit_score_layers(kvs, qs, q_pos0, img, s, a, ws=w)
+
+    score(ws_eager)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        score(ws)
+    for _ in range(4):
+        for k, _, q in L:
+            k.copy_(rnd(*k.shape))
+            q.copy_(rnd(*q.shape))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [t.clone() for t in (lse, s, a)]
+        tail = ws.cpu().numpy()
+        tail = tail[:np.flatnonzero(tail != 0x5a5a5a5a)[-1] + 1]  # less the alignment of its end
+        assert need // 4 - len(tail) < 64
+        assert not tail[-512 * min(layers, 16):].any()  # at least 512 slots per layer of a launch
+        score(ws_eager)
+        torch.cuda.synchronize()
+        for x, y in zip(got, (lse, s, a)):
+            assert torch.equal(x, y)

@@ -441,7 +441,6 @@ conduit_status conduit_score(const conduit_kv *kv, const void *q, int32_t n_q, i
         ap.merge_flag = reinterpret_cast<uint32_t *>(at(ws, L.merge_flag));
         ap.epoch = next_merge_epoch();
       }
-      ap.skip_merge = 1;
       ap.zero_i32 = done;
       ap.zero_n = n_done;
       e = launch_attn(ap, D, false, stream);
@@ -597,7 +596,6 @@ conduit_status conduit_score_layers(const conduit_kv *kvs, int32_t n_layers, con
   ap.plan = plan_at(ws, L.plan);
   ap.part_m = reinterpret_cast<float *>(at(ws, L.plan.part_m));
   ap.part_l = reinterpret_cast<float *>(at(ws, L.plan.part_l));
-  ap.skip_merge = 1;  // merged by the column sums or by the statistics kernel (per launch, below)
   ap.zero_i32 = done;
   ap.zero_n = n_done;
 

@@ -31,6 +31,8 @@
 //     split writes (m, l, O) partials in the log2 domain.
 //  3. combine_kernel merges the partials of split blocks in a fixed order
 //     (deterministic, no atomics).
+// The statistics are the second launch alone: their plan has a closed form,
+// and their splits are merged in the kernel or by the column sums.
 #include <algorithm>
 #include <climits>
 #include <type_traits>
@@ -336,7 +338,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_scatter_kernel(PlanArgs a, 
 // item i mod n of layer i / n (n plan items): layer after layer, each largest
 // item first, so the running workgroups share one or two layers' K/V in the
 // last-level cache.
-template <int D, bool PV, int W, bool UNI, bool ML = false>
+template <int D, bool PV, int W, bool ML>
 __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, LayerTable lt) {
   constexpr int kThreads = W * 64;
   constexpr int kPairs = W * 32;  // (row, head) pairs per block
@@ -420,8 +422,8 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
   float *lse_out = p.lse_out;
   float *row_b = p.row_b;
   const float c = p.scale_log2;
-  // UNI: the closed-form plan of contiguous rows (no plan loads at all).
-  constexpr bool uniform = UNI;
+  // Statistics: the closed-form plan of contiguous rows (no plan loads at all).
+  constexpr bool uniform = !PV;
   const int n_plan_items = uniform ? p.plan.uniform_items : min(p.plan.hdr[0], p.plan.max_items);
   const int n_items = n_plan_items * n_layers;
 
@@ -1220,8 +1222,8 @@ __global__ __launch_bounds__(W * 64, 8 / W) void attn_bf16_kernel(AttnParams p, 
 // order, where Ohat_s = O_s / l_s is the split's own output, kept in bf16 (a
 // convex combination of V rows, so its relative rounding error stays 2^-9
 // and the merged row, a convex combination of the Ohat_s, keeps it).
-// With values a thread merges 16 head dims of one pair (the whole grid is
-// resident at once); statistics only, one thread per pair.  The m_s, l_s and
+// A thread merges 16 head dims of one pair (the whole grid is
+// resident at once).  The m_s, l_s and
 // Ohat_s of up to kMergeBatch splits are loaded together and folded into a
 // running maximum, so a thread waits on two round trips to memory for
 // n_s <= kMergeBatch (plan entry, then the partials); for such blocks the
@@ -1237,26 +1239,23 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineParams p, LayerTabl
     const int64_t off = (int64_t)l * p.plan.max_items * p.ppb;
     p.part_m += off;
     p.part_l += off;
-    if (p.part_o) p.part_o += off * D;
+    p.part_o += off * D;
     p.o_out = lt.o[l];
     p.lse_out = lt.lse[l];
     p.row_b = lt.rowb[l];
   }
   const int64_t n_gp = (int64_t)p.n_rows * p.n_q_heads;
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool values = p.part_o != nullptr;
-  const int64_t gp = values ? gid / NC : gid;
-  const int c = values ? (int)(gid % NC) : 0;
+  const int64_t gp = gid / NC;
+  const int c = (int)(gid % NC);
   if (gp >= n_gp) return;
   const int r = (int)(gp / p.n_q_heads), hq = (int)(gp % p.n_q_heads);
   const int h = hq / p.group;
   const int64_t pair = (int64_t)r * p.group + hq % p.group;
   const int pb = (int)(pair / p.ppb), j = (int)(pair % p.ppb);
-  const bool uniform = p.plan.uniform_ns > 0;
-  const int ns = uniform ? p.plan.uniform_ns : p.plan.pb_info[pb].z;
+  const int ns = p.plan.pb_info[pb].z;
   if (ns <= 1) return;  // written by the attention kernel
-  const int64_t slot0 = uniform ? ((int64_t)pb * (p.n_q_heads / p.group) + h) * ns
-                                : (int64_t)h * p.plan.hdr[1] + p.plan.pb_base[pb];
+  const int64_t slot0 = (int64_t)h * p.plan.hdr[1] + p.plan.pb_base[pb];
   if (slot0 + ns > p.plan.max_items) return;  // never for a plan within its bound
   const int64_t idx0 = slot0 * p.ppb + j;
   // Split s contributes W_s = 2^(m_s - M) l_s and W_s * Ohat_s, with Ohat_s
@@ -1276,7 +1275,7 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineParams p, LayerTabl
       lb[i] = in ? p.part_l[idx] : 0.f;
 #pragma unroll
       for (int q = 0; q < 2; ++q)
-        ob[i][q] = in && values ? ld16(p.part_o + idx * D + kMergeDims * c + 8 * q) : u32x4{0, 0, 0, 0};
+        ob[i][q] = in ? ld16(p.part_o + idx * D + kMergeDims * c + 8 * q) : u32x4{0, 0, 0, 0};
     }
     float Mn = M;
 #pragma unroll
@@ -1307,16 +1306,14 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineParams p, LayerTabl
     if (p.row_b) p.row_b[gp] = b;
     if (p.lse_out) p.lse_out[gp] = b * kLn2;
   }
-  if (values) {
-    const float inv = 1.f / L;
-    u16 *out = static_cast<u16 *>(p.o_out) + gp * D + kMergeDims * c;
+  const float inv = 1.f / L;
+  u16 *out = static_cast<u16 *>(p.o_out) + gp * D + kMergeDims * c;
 #pragma unroll
-    for (int q = 0; q < kMergeDims / 4; ++q) {
-      uint2 w;
-      w.x = (uint32_t)f32_to_bf16(acc[4 * q] * inv) | ((uint32_t)f32_to_bf16(acc[4 * q + 1] * inv) << 16);
-      w.y = (uint32_t)f32_to_bf16(acc[4 * q + 2] * inv) | ((uint32_t)f32_to_bf16(acc[4 * q + 3] * inv) << 16);
-      *reinterpret_cast<uint2 *>(out + 4 * q) = w;
-    }
+  for (int q = 0; q < kMergeDims / 4; ++q) {
+    uint2 w;
+    w.x = (uint32_t)f32_to_bf16(acc[4 * q] * inv) | ((uint32_t)f32_to_bf16(acc[4 * q + 1] * inv) << 16);
+    w.y = (uint32_t)f32_to_bf16(acc[4 * q + 2] * inv) | ((uint32_t)f32_to_bf16(acc[4 * q + 3] * inv) << 16);
+    *reinterpret_cast<uint2 *>(out + 4 * q) = w;
   }
 }
 
@@ -1588,7 +1585,8 @@ hipError_t launch_attn(const AttnParams &p_in, int head_dim, bool with_values, h
   const bool ml = lt0.n > 0;
   const int ppb = attn_pairs_per_block(with_values);
   AttnParams p = p_in;
-  if (!p.row_pos && !with_values) {  // the scoring span: closed-form plan, no plan launch
+  if (!with_values) {  // the scoring span (rows at q_pos0 + r): closed-form plan, no plan launch
+    if (p.row_pos) return hipErrorInvalidValue;
     const int ns = attn_span_splits(p, ppb, ml ? lt0.n : 1);
     const int64_t n_pb = ((int64_t)p.n_rows * p.group + ppb - 1) / ppb;
     p.plan.uniform_ns = ns;
@@ -1599,7 +1597,7 @@ hipError_t launch_attn(const AttnParams &p_in, int head_dim, bool with_values, h
   }
   const PlanArgs pa = plan_args(p, with_values, lt0.n);
   hipError_t e = hipSuccess;
-  if (p.plan.uniform_ns == 0 && !plan_ready) {
+  if (with_values && !plan_ready) {
     ProfScope ps("attn_plan", s);
     attn_plan_kernel<<<1, kPlanThreads, 0, s>>>(pa);
     e = hipGetLastError();
@@ -1609,27 +1607,22 @@ hipError_t launch_attn(const AttnParams &p_in, int head_dim, bool with_values, h
   const int grid = attn_grid(with_values);
   {
     ProfScope ps(with_values ? "attn_values" : "attn_stats", s);
-    // the closed-form plan only serves the statistics of the scoring span
-    const bool uni = p.plan.uniform_ns > 0 && !with_values;
-    if (ml && !with_values && !uni) return hipErrorInvalidValue;  // several layers: refresh or scoring span
     if (head_dim == 128) {
-      if (ml && !with_values) attn_bf16_kernel<128, false, 4, true, true><<<grid, 4 * 64, 0, s>>>(p, lt0);
-      else if (ml) attn_bf16_kernel<128, true, 8, false, true><<<grid, 8 * 64, 0, s>>>(p, lt0);
+      if (ml && !with_values) attn_bf16_kernel<128, false, 4, true><<<grid, 4 * 64, 0, s>>>(p, lt0);
+      else if (ml) attn_bf16_kernel<128, true, 8, true><<<grid, 8 * 64, 0, s>>>(p, lt0);
       else if (with_values) attn_bf16_kernel<128, true, 8, false><<<grid, 8 * 64, 0, s>>>(p, lt0);
-      else if (uni) attn_bf16_kernel<128, false, 4, true><<<grid, 4 * 64, 0, s>>>(p, lt0);
       else attn_bf16_kernel<128, false, 4, false><<<grid, 4 * 64, 0, s>>>(p, lt0);
     } else {
-      if (ml && !with_values) attn_bf16_kernel<64, false, 4, true, true><<<grid, 4 * 64, 0, s>>>(p, lt0);
-      else if (ml) attn_bf16_kernel<64, true, 8, false, true><<<grid, 8 * 64, 0, s>>>(p, lt0);
+      if (ml && !with_values) attn_bf16_kernel<64, false, 4, true><<<grid, 4 * 64, 0, s>>>(p, lt0);
+      else if (ml) attn_bf16_kernel<64, true, 8, true><<<grid, 8 * 64, 0, s>>>(p, lt0);
       else if (with_values) attn_bf16_kernel<64, true, 8, false><<<grid, 8 * 64, 0, s>>>(p, lt0);
-      else if (uni) attn_bf16_kernel<64, false, 4, true><<<grid, 4 * 64, 0, s>>>(p, lt0);
       else attn_bf16_kernel<64, false, 4, false><<<grid, 4 * 64, 0, s>>>(p, lt0);
     }
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
 
-  if (p.skip_merge) return hipSuccess;  // merged by the caller's next kernel
+  if (!with_values) return hipSuccess;  // merged in the kernel, or by the column sums
   CombineParams cp{};
   cp.n_rows = p.n_rows;
   cp.n_q_heads = p.n_q_heads;
@@ -1638,12 +1631,11 @@ hipError_t launch_attn(const AttnParams &p_in, int head_dim, bool with_values, h
   cp.plan = p.plan;
   cp.part_m = p.part_m;
   cp.part_l = p.part_l;
-  cp.part_o = with_values ? p.part_o : nullptr;
+  cp.part_o = p.part_o;
   cp.row_b = p.row_b;
   cp.lse_out = p.lse_out;
-  cp.o_out = with_values ? p.o_out : nullptr;
-  const int64_t n_gp = (int64_t)p.n_rows * p.n_q_heads;
-  const int64_t n = with_values ? n_gp * (head_dim / kMergeDims) : n_gp;
+  cp.o_out = p.o_out;
+  const int64_t n = (int64_t)p.n_rows * p.n_q_heads * (head_dim / kMergeDims);
   const dim3 blocks((unsigned)((n + 255) / 256), ml ? (unsigned)lt0.n : 1u);
   ProfScope ps("attn_merge", s);
   if (head_dim == 128) combine_kernel<128><<<blocks, 256, 0, s>>>(cp, lt0);

